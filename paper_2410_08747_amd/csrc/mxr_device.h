@@ -350,10 +350,11 @@ __device__ __forceinline__ void concentric(double ca, double cb, double &rad, do
 // the cell's square is mapped to the unit disk by the concentric map and the
 // disk radius rho to the cone by sin(theta/2) = rho sin(alpha/2).  Then
 // (dx, dy) = sin(theta) (px, py) / rho = 2 sin(alpha/2) cos(theta/2) (px, py).
-__device__ __forceinline__ void src_cone_beam(const DevComp &c, Stream &s, Ray &ray, uint64_t ray_id,
-                                              const RunArgs &a) {
+// In two parts: the direction (returning the cell's weight factor), and the
+// energy and weight, which a ray that ends before them never needs.
+__device__ __forceinline__ double cone_direction(const DevComp &c, Stream &s, Ray &ray, uint64_t ray_id,
+                                                 const RunArgs &a) {
     const StratCell sc = strat_cell(a.sd, ray_id);
-    const double factor = sc.factor;
     double u = ((double)sc.cx + s.u(0)) * a.sd.rG;
     double v = ((double)sc.cy + s.u(1)) * a.sd.rG;
     double ca = 2.0 * u - 1.0, cb = 2.0 * v - 1.0;
@@ -364,9 +365,17 @@ __device__ __forceinline__ void src_cone_beam(const DevComp &c, Stream &s, Ray &
     double ch = sqrt(1.0 - sh * sh);
     double k = 2.0 * c.aux[0] * ch;
     double dl[3] = {k * px, k * py, 1.0 - 2.0 * (sh * sh)};
+    from_origin(c, dl, ray);
+    return sc.factor;
+}
+__device__ __forceinline__ void cone_energy(const DevComp &c, Stream &s, Ray &ray, double factor) {
     ray.E = c.par[1] + c.aux[1] * s.u(2);
     ray.w = (c.aux[1] * spectrum(c, ray.E)) * factor;
-    from_origin(c, dl, ray);
+}
+__device__ __forceinline__ void src_cone_beam(const DevComp &c, Stream &s, Ray &ray, uint64_t ray_id,
+                                              const RunArgs &a) {
+    const double factor = cone_direction(c, s, ray, ray_id, a);
+    cone_energy(c, s, ray, factor);
 }
 
 // Standard normal truncated to [za, zb] by inversion: the point leaving
@@ -1528,6 +1537,15 @@ __device__ __forceinline__ int64_t bin_of(double x, double lo, double scale, uin
     double f = floor((x - lo) * scale);
     if (!(f >= 0.0 && f < (double)n)) return -1;
     return (int64_t)f;
+}
+
+// Whether a ray reaches the monitor's plane inside its pixels (the energy
+// axis aside): the position test of comp_detector on the same numbers.
+__device__ __forceinline__ bool detector_sees(const DevComp &c, const Ray &ray) {
+    double q[3], dl[3];
+    to_local(c, ray, q, dl);
+    if (!plane_z0(q, dl)) return false;
+    return bin_of(q[0], c.par[0], c.aux[0], c.dims[0]) >= 0 && bin_of(q[1], c.par[2], c.aux[1], c.dims[1]) >= 0;
 }
 
 // returns false if the ray cannot reach the plane; bin = -1 outside
