@@ -2041,6 +2041,10 @@ mxr_status mxr_batch_create(const mxr_batch_job *jobs, uint32_t n_jobs, const mx
         b.n_total = j.n_rays;
         b.seed = j.seed;
         b.word3 = j.job;
+        // the launches form takes the instrument's tile order, as mxr_run does:
+        // contiguous eighths put the cone bands that reach the monitor on two
+        // or three XCDs (8 jobs of 2e7 rays: 18.6 ms, in launch order 7.6 ms)
+        b.xcd_order = ins->order;
         const uint64_t G = strata_side(ins->strata, j.n_rays);
         if (G * G > 1 && j.n_rays > (~0ull - (G * G - 1)) / (G * G))
             return fail(MXR_E_INVALID, "job %u: n_rays * strata^2 + strata^2 - 1 must stay below 2^64", k);
