@@ -115,6 +115,34 @@ __device__ __forceinline__ void append_hit(const RunArgs &a, const DevComp &src,
     a.hits.bin[row] = bin;
 }
 
+__device__ __forceinline__ PhantomGeo phantom_geo(const DevComp &c, const uint8_t *bricks = nullptr) {
+    PhantomGeo g;
+    g.bricks = bricks;
+    g.vol = (const uint8_t *)c.data0;
+    g.n[0] = (int)c.dims[0];
+    g.n[1] = (int)c.dims[1];
+    g.n[2] = (int)c.dims[2];
+    g.v = c.par[0];
+    g.rv = c.aux[6];
+    g.corner[0] = c.aux[0];
+    g.corner[1] = c.aux[1];
+    g.corner[2] = c.aux[2];
+    g.nvox = (uint32_t)c.n0;
+    for (int i = 0; i < 3; ++i) {
+        g.blo[i] = c.aux[8 + i];
+        g.bhi[i] = c.aux[11 + i];
+    }
+    g.bg = (uint32_t)c.aux[14];
+    g.box = c.aux[15] != 0.0;
+    return g;
+}
+
+// Row of the staged attenuation table of an energy.
+__device__ __forceinline__ int mu_row_of(const DevComp &c, double E, uint32_t n_ebin) {
+    const double f = floor((E - c.par[1]) * c.aux[3]);
+    return (int)fmin(fmax(f, 0.0), (double)(n_ebin - 1));
+}
+
 // Apply component k of type T.  Returns false when the ray is absorbed.
 template <int T, bool LEDGER, bool TRACE, bool EXACT, int KW = kWalkRound>
 __device__ __forceinline__ bool apply(const DevComp &c, int k, Ray &ray, Stream &s, uint64_t ray_id,
@@ -150,25 +178,8 @@ __device__ __forceinline__ bool apply(const DevComp &c, int k, Ray &ray, Stream 
         if constexpr (T == MXR_PHANTOM || T == kPhantomStep) {
             double q[3], dl[3];
             to_local(c, ray, q, dl);
-            PhantomGeo g;
-            g.vol = (const uint8_t *)c.data0;
-            g.n[0] = (int)c.dims[0];
-            g.n[1] = (int)c.dims[1];
-            g.n[2] = (int)c.dims[2];
-            g.v = c.par[0];
-            g.rv = c.aux[6];
-            g.corner[0] = c.aux[0];
-            g.corner[1] = c.aux[1];
-            g.corner[2] = c.aux[2];
-            g.nvox = (uint32_t)c.n0;
-            for (int i = 0; i < 3; ++i) {
-                g.blo[i] = c.aux[8 + i];
-                g.bhi[i] = c.aux[11 + i];
-            }
-            g.bg = (uint32_t)c.aux[14];
-            g.box = c.aux[15] != 0.0;
-            double f = floor((ray.E - c.par[1]) * c.aux[3]);
-            int e = (int)fmin(fmax(f, 0.0), (double)(n_ebin - 1));
+            const PhantomGeo g = phantom_geo(c);
+            const int e = mu_row_of(c, ray.E, n_ebin);
             double tau;
             if constexpr (T == kPhantomStep)
                 tau = step_tau(g, q, dl, c.par[3], (int)c.aux[5], mu_lds + e * n_mat);
@@ -256,32 +267,30 @@ __device__ __forceinline__ bool apply_dynamic(const DevComp &c, int k, Ray &ray,
 template <int... Ts>
 struct Chain {};
 
-// Occupancy hint per chain (waves per SIMD the compiler must fit).  The
-// projection chain is latency-bound in its voxel walk: 8 waves (64 VGPRs,
-// a few bytes of scratch for the ray state held across the walk) measured
-// faster than the 6 its natural 76 VGPRs allow.
+// Occupancy hint per chain (waves per SIMD the compiler must fit).  The chains
+// that walk an exact phantom as a bundle hold the scan's and a walk's state at
+// once: 4 waves (126 VGPRs) keep it out of scratch (256^3 projection, 1e9 rays
+// at 0 / 0.785 rad: 29.1 / 31.6 ms; 6 waves with 180 B of scratch 36.8 / 50.6,
+// 8 with 244 B 46.2 / 68.3).  The fixed-step chain fits 8.
 template <class C>
 struct WavesHint {
     static constexpr int value = 1;
 };
-#ifndef MXR_PROJ_WAVES
-#define MXR_PROJ_WAVES 8
-#endif
 template <>
 struct WavesHint<Chain<MXR_SRC_CONE_BEAM, MXR_PHANTOM, MXR_DETECTOR>> {
-    static constexpr int value = MXR_PROJ_WAVES;
+    static constexpr int value = 4;
 };
 template <>
 struct WavesHint<Chain<MXR_SRC_CONE_BEAM, MXR_PHANTOM, kDetectorCollect>> {
-    static constexpr int value = 8;
+    static constexpr int value = 4;
 };
 template <>
 struct WavesHint<Chain<kSrcConeProposal, MXR_PHANTOM, MXR_DETECTOR>> {
-    static constexpr int value = 8;
+    static constexpr int value = 4;
 };
 template <>
 struct WavesHint<Chain<MXR_SRC_CONE_BEAM, MXR_SLIT, MXR_PHANTOM, MXR_DETECTOR>> {
-    static constexpr int value = 8;
+    static constexpr int value = 4;
 };
 template <>
 struct WavesHint<Chain<MXR_SRC_CONE_BEAM, kPhantomStep, MXR_DETECTOR>> {
@@ -293,32 +302,21 @@ template <>
 struct WavesHint<Chain<MXR_SRC_CONE_BEAM, kPhantomScatter, MXR_DETECTOR>> {
     static constexpr int value = 6;
 };
-// Crossings per round of the optical-depth walk, per chain.  The projection's
-// own kernel takes 5 (2-3 % faster than 4 at every angle measured, 12 B of
-// scratch); the chains whose kernels spill more at 5 keep 4 (the early-out
-// projection's kernel ran 1.4x slower at 5, the batch grid 3 % slower).
+// Crossings per round of the optical-depth walk, per chain.
 template <class C>
 struct WalkRound {
     static constexpr int value = kWalkRound;
 };
-template <>
-struct WalkRound<Chain<MXR_SRC_CONE_BEAM, MXR_PHANTOM, MXR_DETECTOR>> {
-    static constexpr int value = 5;
-};
 
 // The batch kernels read their per-job arguments from memory rather than the
-// kernel-argument segment and hold more live values: the projection chain
-// fits 4 waves per SIMD without spilling there.
+// kernel-argument segment; the projection chain takes 4 waves there as well.
 template <class C>
 struct BatchWavesHint {
     static constexpr int value = 1;
 };
-#ifndef MXR_BATCH_WAVES
-#define MXR_BATCH_WAVES 8
-#endif
 template <>
 struct BatchWavesHint<Chain<MXR_SRC_CONE_BEAM, MXR_PHANTOM, MXR_DETECTOR>> {
-    static constexpr int value = MXR_BATCH_WAVES;
+    static constexpr int value = 4;
 };
 
 template <bool LEDGER, bool TRACE, bool EXACT, int KW, int T, int... Rest>
@@ -344,27 +342,61 @@ __device__ __forceinline__ bool run_fixed(const DevInstr *ins, int k, Ray &ray, 
 // bound by VALU issue.
 constexpr bool absorbs_only(int T) { return T == MXR_PHANTOM || T == kPhantomStep; }
 
+// All 64 lanes of a wave call it together (the exact phantom is walked by the
+// wave as a bundle); live: the lane holds a ray.
 template <bool EXACT, int KW, int... Ts>
-__device__ __forceinline__ void run_tallied(Chain<Ts...>, const DevInstr *ins, Ray &ray, Stream &s, uint64_t ray_id,
-                                            const RunArgs &a, const double *mu_lds, uint32_t n_mat, uint32_t n_ebin,
-                                            RayEnd &end, const LedgerLds &L) {
+__device__ __forceinline__ void run_tallied(Chain<Ts...>, const DevInstr *ins, Stream &s, uint64_t ray_id, bool live,
+                                            const RunArgs &a, const double *mu_lds, uint32_t n_mat, uint32_t n_ebin) {
     constexpr int N = sizeof...(Ts);
     constexpr int T[N] = {Ts...};
+    const LedgerLds L{nullptr};
+    RayEnd end{kExited, -1, -1};
+    Ray ray;
+    ray.r[0] = ray.r[1] = ray.r[2] = 0.0;
+    ray.d[0] = ray.d[1] = ray.d[2] = 0.0;
+    ray.E = 0.0;
+    ray.w = 0.0;
     double factor = 0.0;
     if constexpr (T[0] == MXR_SRC_CONE_BEAM) factor = cone_direction(ins->c[0], s, ray, ray_id, a);
-    else if (!apply<T[0], false, false, EXACT, KW>(ins->c[0], 0, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L)) return;
+    else live = apply<T[0], false, false, EXACT, KW>(ins->c[0], 0, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L) && live;
     if constexpr (N == 4) {
         static_assert(T[1] == MXR_SLIT, "an aperture between the source and the phantom");
-        if (!comp_slit(ins->c[1], ray)) return;
+        live = comp_slit(ins->c[1], ray) && live;
     }
-    if (!detector_sees(ins->c[N - 1], ray)) return;
+    const DevComp &det = ins->c[N - 1];
+    const int64_t pixel = detector_pixel(det, ray);
+    live = live && pixel >= 0;
+    if (__builtin_amdgcn_ballot_w64(live) == 0) return;
     if constexpr (T[0] == MXR_SRC_CONE_BEAM) cone_energy(ins->c[0], s, ray, factor);
-    (void)apply<T[N - 2], false, false, EXACT, KW>(ins->c[N - 2], N - 2, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
-    (void)apply<T[N - 1], false, false, EXACT, KW>(ins->c[N - 1], N - 1, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+    const int64_t ie = detector_energy_bin(det, ray.E);
+    live = live && ie >= 0;
+    const int64_t bin = pixel * (int64_t)det.dims[2] + ie;
+    const DevComp &ph = ins->c[N - 2];
+    const PhantomGeo g = phantom_geo(ph, ins->bricks);
+    double q[3], dl[3];
+    to_local(ph, ray, q, dl);
+    const double *mu_row = mu_lds + mu_row_of(ph, ray.E, n_ebin) * n_mat;
+    double tau = 0.0;
+    if constexpr (T[N - 2] == kPhantomStep) {
+        if (live) tau = step_tau(g, q, dl, ph.par[3], (int)ph.aux[5], mu_row);
+    } else {
+        double inv[3], a_in, a_out;
+        const bool in = live && volume_chord(g, q, dl, inv, a_in, a_out);
+        tau = bundle_tau<EXACT>(g, q, dl, inv, a_in, a_out, in, mu_row);
+        tau = in ? tau : 0.0;
+    }
+    if (live) {
+        ray.w = ray.w * exp(-tau);
+        if constexpr (T[N - 1] == kDetectorCollect) append_hit(a, ins->c[0], ray, bin, true);
+        const uint32_t sl = det.slot;
+        atomicAdd(a.tally.count[sl] + bin, 1ull);
+        atomicAdd(a.tally.sum_w[sl] + bin, ray.w);
+        atomicAdd(a.tally.sum_w2[sl] + bin, ray.w * ray.w);
+    }
 }
 
 template <int... Ts>
-constexpr bool ends_in_absorber() {
+constexpr bool ends_in_absorber(Chain<Ts...>) {
     constexpr int N = sizeof...(Ts);
     constexpr int T[N] = {Ts...};
     if constexpr (N == 3 || N == 4) return absorbs_only(T[N - 2]) && is_detector(T[N - 1]);
@@ -380,9 +412,6 @@ __device__ __forceinline__ bool run_chain(Chain<Ts...>, const DevInstr *ins, Ray
         for (uint32_t k = 0; k < n; ++k)
             if (!apply_dynamic<LEDGER, TRACE, EXACT, KW>(ins->c[k], (int)k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L))
                 return false;
-        return true;
-    } else if constexpr (!LEDGER && !TRACE && ends_in_absorber<Ts...>()) {
-        run_tallied<EXACT, KW>(Chain<Ts...>{}, ins, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
         return true;
     } else {
         return run_fixed<LEDGER, TRACE, EXACT, KW, Ts...>(ins, 0, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
@@ -445,6 +474,14 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_trace(const MXR_CONSTANT_PARA
 
     const uint64_t logical = tile_of(blockIdx.x, a.xcd_order, a.blocks_per_xcd);
     const uint64_t i = logical * kBlock + threadIdx.x;
+    if constexpr (!LEDGER && !TRACE && ends_in_absorber(C{})) {
+        // every lane takes part; past the range it holds the last ray, dead
+        const uint64_t ray_id = a.first + (i < a.n ? i : a.n - 1);
+        Stream s;
+        s.init(a.seed, ray_id, a.word3);
+        run_tallied<EXACT, WalkRound<C>::value>(C{}, ins, s, ray_id, i < a.n, a, mu_lds, n_mat, n_ebin);
+        return;
+    }
     if (i < a.n) {
         const uint64_t ray_id = TRACE ? a.ids[i] : a.first + i;
         Stream s;
@@ -711,16 +748,23 @@ __global__ __launch_bounds__(kBlock, BatchWavesHint<C>::value) void k_batch(cons
         }
         const uint64_t r0 = (tile - J.tile0) * tile_rays;
         const uint64_t r1 = r0 + tile_rays < a.n ? r0 + tile_rays : a.n;
-        for (uint64_t ray_id = r0 + threadIdx.x; ray_id < r1; ray_id += kBlock) {
-            Stream s;
-            s.init(a.seed, ray_id, a.word3);
-            Ray ray;
-            ray.r[0] = ray.r[1] = ray.r[2] = 0.0;
-            ray.d[0] = ray.d[1] = ray.d[2] = 0.0;
-            ray.E = 0.0;
-            ray.w = 0.0;
-            RayEnd end{kExited, -1, -1};
-            run_chain<false, false, EXACT>(C{}, ins, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+        if constexpr (ends_in_absorber(C{})) {
+            for (uint64_t r = r0; r < r1; r += kBlock) {  // every lane takes part
+                const bool live = r + threadIdx.x < r1;
+                const uint64_t ray_id = live ? r + threadIdx.x : r1 - 1;
+                Stream s;
+                s.init(a.seed, ray_id, a.word3);
+                run_tallied<EXACT, kWalkRound>(C{}, ins, s, ray_id, live, a, mu_lds, n_mat, n_ebin);
+            }
+        } else {
+            for (uint64_t ray_id = r0 + threadIdx.x; ray_id < r1; ray_id += kBlock) {
+                Stream s;
+                s.init(a.seed, ray_id, a.word3);
+                Ray ray;
+                fresh_ray(ray);
+                RayEnd end{kExited, -1, -1};
+                run_chain<false, false, EXACT>(C{}, ins, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+            }
         }
         // the next tile may restage the table: everyone must be done with it
         __syncthreads();
@@ -761,18 +805,21 @@ __global__ __launch_bounds__(kBlock, BatchWavesHint<C>::value) void k_batch_grid
         for (uint32_t i = threadIdx.x; i < n_mu; i += kBlock) mu_lds[i] = T[i];
     }
     __syncthreads();
-    const uint64_t ray_id = (tile - jobs[lo].tile0) * kBlock + threadIdx.x;
-    if (ray_id >= a.n) return;
-    const LedgerLds L{nullptr};
+    const uint64_t id = (tile - jobs[lo].tile0) * kBlock + threadIdx.x;
     Stream s;
-    s.init(a.seed, ray_id, a.word3);
-    Ray ray;
-    ray.r[0] = ray.r[1] = ray.r[2] = 0.0;
-    ray.d[0] = ray.d[1] = ray.d[2] = 0.0;
-    ray.E = 0.0;
-    ray.w = 0.0;
-    RayEnd end{kExited, -1, -1};
-    run_chain<false, false, EXACT>(C{}, ins, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+    if constexpr (ends_in_absorber(C{})) {
+        const uint64_t ray_id = id < a.n ? id : a.n - 1;  // every lane takes part
+        s.init(a.seed, ray_id, a.word3);
+        run_tallied<EXACT, kWalkRound>(C{}, ins, s, ray_id, id < a.n, a, mu_lds, n_mat, n_ebin);
+    } else {
+        if (id >= a.n) return;
+        const LedgerLds L{nullptr};
+        s.init(a.seed, id, a.word3);
+        Ray ray;
+        fresh_ray(ray);
+        RayEnd end{kExited, -1, -1};
+        run_chain<false, false, EXACT>(C{}, ins, ray, s, id, a, mu_lds, n_mat, n_ebin, end, L);
+    }
 }
 
 // The phantom's attenuation table in the form the kernels stage (run once at
@@ -785,45 +832,61 @@ __global__ __launch_bounds__(kBlock) void k_mu_energy_major(const double *T, uin
     out[e * n_mat + m] = T[i] * 0.1;
 }
 
-// One pass over a phantom (run once at create), one row of x per lane: the
-// largest material id, and the box of the voxels whose material differs from
-// the corner voxel's.  out[0] = largest id, out[1..3] = least x, y, z of such
-// a voxel, out[4..6] = largest x, y, z + 1, out[7] = the corner's material
-// (out[1..3] start at ~0 and out[0], out[4..6] at 0).
+// One pass over a phantom (run once at create), one brick of 4^3 voxels per
+// lane: the brick map (see DevInstr), the largest material id, and the box
+// of the voxels whose material differs from the corner voxel's.  out[0] =
+// largest id, out[1..3] = least x, y, z of such a voxel, out[4..6] = largest
+// x, y, z + 1, out[7] = the corner's material (out[1..3] start at ~0 and
+// out[0], out[4..6] at 0).  WORDS: rows of x start at multiples of four bytes,
+// so a brick's row is one 32-bit load (a 512^3 volume in one pass of
+// neighbouring loads; a lane per row of single bytes took 584 us there).
+template <bool WORDS>
 __global__ __launch_bounds__(kBlock) void k_phantom_scan(const uint8_t *vol, uint32_t nx, uint32_t ny, uint32_t nz,
-                                                        unsigned int *out) {
+                                                        uint8_t *bricks, unsigned int *out) {
     __shared__ unsigned int red[7];
     if (threadIdx.x < 7) red[threadIdx.x] = (threadIdx.x >= 1 && threadIdx.x <= 3) ? ~0u : 0u;
     __syncthreads();
     const uint32_t bg = vol[0];
-    const uint32_t rows = ny * nz;
+    const uint32_t bx = (nx + 3) / 4, by = (ny + 3) / 4, bz = (nz + 3) / 4;
+    const uint32_t n = bx * by * bz;  // at most 2^31 voxels and 2^20 + 9 layers: below 2^32
     unsigned int mx = 0, lo[3] = {~0u, ~0u, ~0u}, hi[3] = {0u, 0u, 0u};
-    for (uint32_t r = blockIdx.x * kBlock + threadIdx.x; r < rows; r += gridDim.x * kBlock) {
-        const uint8_t *row = vol + (uint64_t)r * nx;
-        uint32_t first = nx, last = 0;
-        for (uint32_t x = 0; x < nx; ++x) {
-            const uint32_t m = row[x];
-            mx = m > mx ? m : mx;
-            if (m != bg) {
-                first = x < first ? x : first;
-                last = x + 1;
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+        const uint32_t x0 = (i % bx) * 4, y0 = (i / bx) % by * 4, z0 = i / bx / by * 4;
+        const uint32_t x1 = x0 + 4 < nx ? x0 + 4 : nx, y1 = y0 + 4 < ny ? y0 + 4 : ny, z1 = z0 + 4 < nz ? z0 + 4 : nz;
+        const uint32_t m0 = vol[((uint64_t)z0 * ny + y0) * nx + x0];
+        uint32_t differ = 0;
+        for (uint32_t z = z0; z < z1; ++z)
+            for (uint32_t y = y0; y < y1; ++y) {
+                const uint8_t *row = vol + ((uint64_t)z * ny + y) * nx + x0;
+                uint32_t w = m0 * 0x01010101u;
+                if constexpr (WORDS) {
+                    w = *(const uint32_t *)row;
+                } else {
+                    for (uint32_t x = 0; x < x1 - x0; ++x) w = (w & ~(0xFFu << (8 * x))) | ((uint32_t)row[x] << (8 * x));
+                }
+                const uint32_t d = w ^ (m0 * 0x01010101u);
+                differ |= d;
+                for (uint32_t x = 0; x < 4; ++x) mx = ((w >> (8 * x)) & 0xFFu) > mx ? (w >> (8 * x)) & 0xFFu : mx;
+                // first and last byte of the row that is not background
+                const uint32_t e = (w ^ (bg * 0x01010101u)) & (~0u >> (8 * (4 - (x1 - x0))));
+                if (e != 0) {
+                    const uint32_t first = x0 + (uint32_t)__builtin_ctz(e) / 8, last = x0 + (31 - (uint32_t)__builtin_clz(e)) / 8 + 1;
+                    lo[0] = first < lo[0] ? first : lo[0];
+                    hi[0] = last > hi[0] ? last : hi[0];
+                    lo[1] = y < lo[1] ? y : lo[1];
+                    hi[1] = y + 1 > hi[1] ? y + 1 : hi[1];
+                    lo[2] = z < lo[2] ? z : lo[2];
+                    hi[2] = z + 1 > hi[2] ? z + 1 : hi[2];
+                }
             }
-        }
-        if (last > 0) {
-            const uint32_t z = r / ny, y = r - z * ny;
-            lo[0] = first < lo[0] ? first : lo[0];
-            hi[0] = last > hi[0] ? last : hi[0];
-            lo[1] = y < lo[1] ? y : lo[1];
-            hi[1] = y + 1 > hi[1] ? y + 1 : hi[1];
-            lo[2] = z < lo[2] ? z : lo[2];
-            hi[2] = z + 1 > hi[2] ? z + 1 : hi[2];
-        }
+        bricks[i] = differ ? (uint8_t)255 : (uint8_t)m0;
     }
     atomicMax(&red[0], mx);
-    for (int d = 0; d < 3; ++d) {
-        atomicMin(&red[1 + d], lo[d]);
-        atomicMax(&red[4 + d], hi[d]);
-    }
+    if (hi[0] > 0)
+        for (int d = 0; d < 3; ++d) {
+            atomicMin(&red[1 + d], lo[d]);
+            atomicMax(&red[4 + d], hi[d]);
+        }
     __syncthreads();
     if (threadIdx.x == 0) {
         atomicMax(out, red[0]);
@@ -1054,7 +1117,7 @@ struct mxr_instrument {
     uint64_t strata;      // G of the cone-beam source, 0 if none
     int n_cu;             // compute units of the device
     PropTable *prop_dev;  // proposal mixture (device), allocated on first use
-    double *mu_dev;       // the phantom's staged attenuation table (device), or null
+    double *mu_dev;       // the phantom's staged attenuation table and brick map (device), or null
     PropTable prop_host;  // its host copy (branch sizes are set per run)
     bool prop_on;
 };
@@ -1325,12 +1388,16 @@ mxr_status mxr_instrument_create(const mxr_instrument_desc *desc, mxr_instrument
         ins->n_cu = 256;
     ins->mu_dev = nullptr;
     if (d.phantom >= 0) {
+        // the staged attenuation table, and the brick map behind it
         const uint32_t n_mu = d.n_mat * d.n_ebin;
-        e = hipMalloc((void **)&ins->mu_dev, (size_t)n_mu * sizeof(double));
+        const uint32_t *dims = d.c[d.phantom].dims;
+        const size_t n_bricks = (size_t)((dims[0] + 3) / 4) * ((dims[1] + 3) / 4) * ((dims[2] + 3) / 4);
+        e = hipMalloc((void **)&ins->mu_dev, (size_t)n_mu * sizeof(double) + n_bricks);
         if (e != hipSuccess) {
             delete ins;
             return fail(MXR_E_NOMEM, "hipMalloc of the attenuation table: %s", hipGetErrorString(e));
         }
+        d.bricks = (const uint8_t *)(ins->mu_dev + n_mu);
         hipLaunchKernelGGL(k_mu_energy_major, dim3((n_mu + kBlock - 1) / kBlock), dim3(kBlock), 0, 0,
                            (const double *)d.c[d.phantom].data1, d.n_mat, d.n_ebin, ins->mu_dev);
         e = hipGetLastError();
@@ -1349,10 +1416,11 @@ mxr_status mxr_instrument_create(const mxr_instrument_desc *desc, mxr_instrument
         e = hipMalloc((void **)&dscan, sizeof hs);
         if (e == hipSuccess) e = hipMemcpy(dscan, hs, sizeof hs, hipMemcpyHostToDevice);
         if (e == hipSuccess) {
-            const uint64_t rows = (uint64_t)c.dims[1] * c.dims[2];
-            const uint64_t nb = std::min<uint64_t>((rows + kBlock - 1) / kBlock, 4096);
-            hipLaunchKernelGGL(k_phantom_scan, dim3((unsigned)nb), dim3(kBlock), 0, 0, (const uint8_t *)c.data0,
-                               c.dims[0], c.dims[1], c.dims[2], dscan);
+            const uint64_t nb = (uint64_t)((c.dims[0] + 3) / 4) * ((c.dims[1] + 3) / 4) * ((c.dims[2] + 3) / 4);
+            const unsigned groups = (unsigned)std::min<uint64_t>((nb + kBlock - 1) / kBlock, 2048);
+            const bool words = c.dims[0] % 4 == 0 && ((uintptr_t)c.data0 & 3) == 0;
+            hipLaunchKernelGGL(words ? k_phantom_scan<true> : k_phantom_scan<false>, dim3(groups), dim3(kBlock), 0, 0,
+                               (const uint8_t *)c.data0, c.dims[0], c.dims[1], c.dims[2], (uint8_t *)d.bricks, dscan);
             e = hipGetLastError();
         }
         if (e == hipSuccess) e = hipMemcpy(hs, dscan, sizeof hs, hipMemcpyDeviceToHost);
