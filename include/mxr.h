@@ -217,13 +217,13 @@ const char *mxr_last_error(void);
 
 /* Validates desc, derives per-component constants and copies them to the
  * current device (small allocations owned by the handle: the constants and,
- * for a phantom, a copy of its attenuation table per mm and energy-major,
- * the form the kernels stage in LDS): the
- * instrument as a sequence of components placed in the lab frame (paper,
- * section 2.1), its component data held in structs and made available on
- * the device once (section 2.2.2).  The data
- * arrays are referenced, not copied: they must stay alive and unchanged
- * while the handle is used.  Errors: MXR_E_INVALID (null pointers, wrong
+ * for a phantom, a copy of its attenuation table per mm and energy-major, the
+ * form the kernels stage in LDS, and a map of its uniform 4 x 4 x 4 bricks, a
+ * byte each): the instrument as a sequence of components placed in the lab
+ * frame (paper, section 2.1), its component data held in structs and made
+ * available on the device once (section 2.2.2).  The data arrays are
+ * referenced, not copied: they must stay alive and unchanged while the handle
+ * is used.  Errors: MXR_E_INVALID (null pointers, wrong
  * version, bad component order, non-finite or out-of-range parameters),
  * MXR_E_UNSUPPORTED (limits above), MXR_E_NOMEM, MXR_E_HIP. */
 mxr_status mxr_instrument_create(const mxr_instrument_desc *desc, mxr_instrument **out);
@@ -242,7 +242,7 @@ void mxr_instrument_destroy(mxr_instrument *ins);
  *   compact    1: chains with a crop right after the source run the
  *              survivor-compacting kernel; 0: one ray per lane
  *   rounds     compacting kernel: 64-ray rounds per wave, 1..64 (0 = 64)
- *   xcd_order  which 256-ray tiles each of the eight XCDs traces: 0, the
+ *   xcd_order  which ray tiles (256 rays; projections up to 4096) each of the eight XCDs traces: 0, the
  *              i-th XCD the i-th eighth of the ray range; 1, launch order;
  *              2, runs of 64 consecutive tiles dealt to the XCDs in turn.
  *              The default is 1 for instruments with a phantom (the

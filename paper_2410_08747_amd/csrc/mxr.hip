@@ -4,10 +4,9 @@
 // ray from the source through every component to the monitors with all
 // state in registers (paper, section 2.2: independent rays, local
 // intermediates; the monitor arrays are the only shared data and are updated
-// atomically).  The launch is XCD-aware: work-groups are dealt to the eight
-// XCDs round-robin, so work-group b works on the (b mod 8)-th eighth of the
-// ray range and neighbouring ray ids -- which the stratified cone-beam
-// source sends through neighbouring voxels -- share one XCD's L2.
+// atomically).  Projections -- a cone beam, a phantom that absorbs and a
+// monitor -- trace tiles of neighbouring source cells instead of runs of ray
+// ids (the image kernel); tile_of says which XCD traces what.
 //
 // Component sequences that the library knows are compiled as fixed chains
 // (no per-component dispatch); any other sequence of supported components
@@ -31,14 +30,6 @@ using namespace mxr;
 
 namespace {
 
-// The device's constant address space, for tables that no kernel writes
-// while they are read (in the host pass, where kernel bodies are only
-// parsed, it is the ordinary one).
-#if defined(__HIP_DEVICE_COMPILE__)
-#define MXR_CONSTANT __attribute__((address_space(4)))
-#else
-#define MXR_CONSTANT
-#endif
 // The same space for a kernel's pointer parameter, in both passes: a
 // parameter's type is part of the kernel's mangled name, by which the host
 // stub finds the device code, so host and device must spell it alike.
@@ -113,28 +104,6 @@ __device__ __forceinline__ void append_hit(const RunArgs &a, const DevComp &src,
     a.hits.y[row * 3 + 2] = ray.E;
     a.hits.w[row] = ray.w;
     a.hits.bin[row] = bin;
-}
-
-__device__ __forceinline__ PhantomGeo phantom_geo(const DevComp &c, const uint8_t *bricks = nullptr) {
-    PhantomGeo g;
-    g.bricks = bricks;
-    g.vol = (const uint8_t *)c.data0;
-    g.n[0] = (int)c.dims[0];
-    g.n[1] = (int)c.dims[1];
-    g.n[2] = (int)c.dims[2];
-    g.v = c.par[0];
-    g.rv = c.aux[6];
-    g.corner[0] = c.aux[0];
-    g.corner[1] = c.aux[1];
-    g.corner[2] = c.aux[2];
-    g.nvox = (uint32_t)c.n0;
-    for (int i = 0; i < 3; ++i) {
-        g.blo[i] = c.aux[8 + i];
-        g.bhi[i] = c.aux[11 + i];
-    }
-    g.bg = (uint32_t)c.aux[14];
-    g.box = c.aux[15] != 0.0;
-    return g;
 }
 
 // Row of the staged attenuation table of an energy.
@@ -270,7 +239,7 @@ struct Chain {};
 // Occupancy hint per chain (waves per SIMD the compiler must fit).  The chains
 // that walk an exact phantom as a bundle hold the scan's and a walk's state at
 // once: 4 waves (126 VGPRs) keep it out of scratch (256^3 projection, 1e9 rays
-// at 0 / 0.785 rad: 29.1 / 31.6 ms; 6 waves with 180 B of scratch 36.8 / 50.6,
+// at 0 / 0.785 rad, a ray id per lane: 29.1 / 31.6 ms; 6 waves with 180 B of scratch 36.8 / 50.6,
 // 8 with 244 B 46.2 / 68.3).  The fixed-step chain fits 8.
 template <class C>
 struct WavesHint {
@@ -301,11 +270,6 @@ struct WavesHint<Chain<MXR_SRC_CONE_BEAM, kPhantomStep, MXR_DETECTOR>> {
 template <>
 struct WavesHint<Chain<MXR_SRC_CONE_BEAM, kPhantomScatter, MXR_DETECTOR>> {
     static constexpr int value = 6;
-};
-// Crossings per round of the optical-depth walk, per chain.
-template <class C>
-struct WalkRound {
-    static constexpr int value = kWalkRound;
 };
 
 // The batch kernels read their per-job arguments from memory rather than the
@@ -343,10 +307,20 @@ __device__ __forceinline__ bool run_fixed(const DevInstr *ins, int k, Ray &ray, 
 constexpr bool absorbs_only(int T) { return T == MXR_PHANTOM || T == kPhantomStep; }
 
 // All 64 lanes of a wave call it together (the exact phantom is walked by the
-// wave as a bundle); live: the lane holds a ray.
+// wave as a bundle); live: the lane holds a ray.  hit.live: the ray is to be
+// tallied.
+struct TallyHit {
+    bool live;
+    uint32_t ix, iy, ie;
+    int64_t bin;
+    double w;
+};
+
 template <bool EXACT, int KW, int... Ts>
-__device__ __forceinline__ void run_tallied(Chain<Ts...>, const DevInstr *ins, Stream &s, uint64_t ray_id, bool live,
-                                            const RunArgs &a, const double *mu_lds, uint32_t n_mat, uint32_t n_ebin) {
+__device__ __forceinline__ TallyHit run_tallied(Chain<Ts...>, const DevInstr *ins, uint64_t ray_id, bool live,
+                                                const RunArgs &a, const double *mu_lds, uint32_t n_mat, uint32_t n_ebin) {
+    Stream s;
+    s.init(a.seed, ray_id, a.word3);
     constexpr int N = sizeof...(Ts);
     constexpr int T[N] = {Ts...};
     const LedgerLds L{nullptr};
@@ -364,35 +338,43 @@ __device__ __forceinline__ void run_tallied(Chain<Ts...>, const DevInstr *ins, S
         live = comp_slit(ins->c[1], ray) && live;
     }
     const DevComp &det = ins->c[N - 1];
-    const int64_t pixel = detector_pixel(det, ray);
-    live = live && pixel >= 0;
-    if (__builtin_amdgcn_ballot_w64(live) == 0) return;
+    TallyHit hit;
+    live = detector_pixel(det, ray, hit.ix, hit.iy) && live;
+    hit.live = false;
+    if (__builtin_amdgcn_ballot_w64(live) == 0) return hit;
     if constexpr (T[0] == MXR_SRC_CONE_BEAM) cone_energy(ins->c[0], s, ray, factor);
     const int64_t ie = detector_energy_bin(det, ray.E);
     live = live && ie >= 0;
-    const int64_t bin = pixel * (int64_t)det.dims[2] + ie;
+    hit.live = live;
+    hit.ie = (uint32_t)ie;
+    hit.bin = ((int64_t)hit.iy * (int64_t)det.dims[0] + (int64_t)hit.ix) * (int64_t)det.dims[2] + ie;
     const DevComp &ph = ins->c[N - 2];
-    const PhantomGeo g = phantom_geo(ph, ins->bricks);
     double q[3], dl[3];
     to_local(ph, ray, q, dl);
     const double *mu_row = mu_lds + mu_row_of(ph, ray.E, n_ebin) * n_mat;
     double tau = 0.0;
     if constexpr (T[N - 2] == kPhantomStep) {
-        if (live) tau = step_tau(g, q, dl, ph.par[3], (int)ph.aux[5], mu_row);
+        if (live) tau = step_tau(phantom_geo(ph), q, dl, ph.par[3], (int)ph.aux[5], mu_row);
     } else {
         double inv[3], a_in, a_out;
-        const bool in = live && volume_chord(g, q, dl, inv, a_in, a_out);
-        tau = bundle_tau<EXACT>(g, q, dl, inv, a_in, a_out, in, mu_row);
+        const bool in = live && volume_chord(phantom_geo(ph), q, dl, inv, a_in, a_out);
+        tau = bundle_tau<EXACT>((const MXR_CONSTANT DevComp *)&ph, (const MXR_CONSTANT uint8_t *)ins->bricks, q, dl, inv, a_in, a_out, in,
+                                mu_row);
         tau = in ? tau : 0.0;
     }
     if (live) {
         ray.w = ray.w * exp(-tau);
-        if constexpr (T[N - 1] == kDetectorCollect) append_hit(a, ins->c[0], ray, bin, true);
-        const uint32_t sl = det.slot;
-        atomicAdd(a.tally.count[sl] + bin, 1ull);
-        atomicAdd(a.tally.sum_w[sl] + bin, ray.w);
-        atomicAdd(a.tally.sum_w2[sl] + bin, ray.w * ray.w);
+        if constexpr (T[N - 1] == kDetectorCollect) append_hit(a, ins->c[0], ray, hit.bin, true);
     }
+    hit.w = ray.w;
+    return hit;
+}
+
+__device__ __forceinline__ void tally_global(const RunArgs &a, uint32_t slot, const TallyHit &hit) {
+    if (!hit.live) return;
+    atomicAdd(a.tally.count[slot] + hit.bin, 1ull);
+    atomicAdd(a.tally.sum_w[slot] + hit.bin, hit.w);
+    atomicAdd(a.tally.sum_w2[slot] + hit.bin, hit.w * hit.w);
 }
 
 template <int... Ts>
@@ -474,14 +456,6 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_trace(const MXR_CONSTANT_PARA
 
     const uint64_t logical = tile_of(blockIdx.x, a.xcd_order, a.blocks_per_xcd);
     const uint64_t i = logical * kBlock + threadIdx.x;
-    if constexpr (!LEDGER && !TRACE && ends_in_absorber(C{})) {
-        // every lane takes part; past the range it holds the last ray, dead
-        const uint64_t ray_id = a.first + (i < a.n ? i : a.n - 1);
-        Stream s;
-        s.init(a.seed, ray_id, a.word3);
-        run_tallied<EXACT, WalkRound<C>::value>(C{}, ins, s, ray_id, i < a.n, a, mu_lds, n_mat, n_ebin);
-        return;
-    }
     if (i < a.n) {
         const uint64_t ray_id = TRACE ? a.ids[i] : a.first + i;
         Stream s;
@@ -492,7 +466,7 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_trace(const MXR_CONSTANT_PARA
         ray.E = 0.0;
         ray.w = 0.0;
         RayEnd end{kExited, -1, -1};
-        bool alive = run_chain<LEDGER, TRACE, EXACT, WalkRound<C>::value>(C{}, ins, ray, s, ray_id, a, mu_lds, n_mat,
+        bool alive = run_chain<LEDGER, TRACE, EXACT, kWalkRound>(C{}, ins, ray, s, ray_id, a, mu_lds, n_mat,
                                                                           n_ebin, end, L);
         if constexpr (LEDGER) {
             if (alive) atomicAdd(L.slots + 4 * ins->ncomp, ray.w);
@@ -517,6 +491,128 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_trace(const MXR_CONSTANT_PARA
         for (uint32_t k = threadIdx.x; k < n_slots; k += kBlock) {
             double v = L.slots[k];
             if (v != 0.0) atomicAdd(a.ledger + k, v);
+        }
+    }
+}
+
+// -------------------------------------------------------- image kernel --
+// Plain and collecting runs of the chains that run_tallied carries.  A
+// work-group traces one tile of 256 << rounds rays (see TileRange): rays of
+// neighbouring cells in both directions, so that a wave's bundle is as narrow
+// as its rays allow and the tile's rays fall on few pixels.
+//   - A tile of a plain cone whose rays all miss the monitor ends at once.
+//   - The tile's histogram is kept in LDS, direct-mapped over a window of
+//     2^lx x 2^ly pixels (slot tags: the bin + 1), and added to the caller's
+//     once per tile; a bin whose slot another bin holds goes straight to the
+//     caller's.  Three atomics per detected ray had bound the kernel: 1e9 rays
+//     take 27 ms at the 3.3e10 atomics a second that go past the L2s.
+// Every loop is bounded by the tile's rays and every wave reaches the barriers.
+struct LdsTally {
+    uint32_t *tag, *count;
+    double *w, *w2;
+};
+__device__ __forceinline__ LdsTally lds_tally(double *smem, uint32_t slots) {
+    LdsTally t;
+    t.w = smem;
+    t.w2 = smem + slots;
+    t.tag = (uint32_t *)(smem + 2 * slots);
+    t.count = t.tag + slots;
+    return t;
+}
+
+// First ray id of a row.
+__device__ __forceinline__ uint64_t row_start(const TileRange &r, uint32_t row) {
+    const uint64_t x = (uint64_t)row * r.rem + r.rows - 1;
+    return r.first + (uint64_t)row * r.q + div_est(x, r.rows, r.r_rows, r.rows);
+}
+
+template <class C, bool EXACT, int WAVES = WavesHint<C>::value>
+__global__ __launch_bounds__(kBlock, WAVES) void k_image(const MXR_CONSTANT_PARAM DevInstr *__restrict__ insc,
+                                                         RunArgs a) {
+    const DevInstr *ins = (const DevInstr *)insc;  // as in k_trace
+    extern __shared__ double smem[];
+    uint64_t tile = a.tp.first_tile + tile_of(blockIdx.x, a.xcd_order, a.blocks_per_xcd);
+    if (tile >= a.tp.tiles) return;  // whole work-group
+    uint32_t ri = 0;
+    while (ri + 1 < a.tp.ranges && tile >= a.tp.r[ri].tiles) {
+        tile -= a.tp.r[ri].tiles;
+        ++ri;
+    }
+    const TileRange &r = a.tp.r[ri];
+    const uint32_t per_row = (256u << a.tp.rounds) >> r.ht;  // ids of a tile's row
+    const uint64_t block = div_est(tile, r.cols, r.r_cols, r.rows);
+    const uint64_t col0 = (tile - block * r.cols) * per_row;
+    const uint32_t row0 = (uint32_t)(block << r.ht);
+    const DevComp &det = ins->c[ins->ncomp - 1];
+    if (a.tp.cull) {
+        // the tile's cells: rows of cells are rows of ids, and the id at
+        // place o of a row lies in cell floor(o G^2 / n + x), 0 <= x < G^2 / n
+        const double per = (double)a.sd.G2 * a.sd.rn, G = (double)a.sd.G;
+        const double last = (double)(col0 + per_row < r.q + 1 ? col0 + per_row - 1 : r.q);
+        const double u0 = 2.0 * (floor((double)col0 * per - 1e-6) / G) - 1.0;
+        const double u1 = 2.0 * ((floor((last + 1.0) * per + 1e-6) + 1.0) / G) - 1.0;
+        const uint32_t row1 = row0 + (1u << r.ht) < r.rows ? row0 + (1u << r.ht) : r.rows;
+        const double v0 = 2.0 * ((double)row0 / G) - 1.0, v1 = 2.0 * ((double)row1 / G) - 1.0;
+        if (bundle_misses(ins->c[0], det, 0.5 * (u0 + u1), 0.5 * (v0 + v1), 0.5 * (u1 - u0) + 1e-9, 0.5 * (v1 - v0) + 1e-9))
+            return;  // whole work-group
+    }
+    const uint32_t n_mat = ins->n_mat, n_ebin = ins->n_ebin, n_mu = n_mat * n_ebin;
+    double *mu_lds = smem;
+    {
+        const double *T = ins->mu_em;
+        for (uint32_t i = threadIdx.x; i < n_mu; i += kBlock) mu_lds[i] = T[i];
+    }
+    const uint32_t ne = a.tp.lds_ne, slots = ne << (a.tp.lx + a.tp.ly);
+    const LdsTally L = lds_tally(smem + n_mu, slots);
+    for (uint32_t i = threadIdx.x; i < slots; i += kBlock) {
+        L.w[i] = 0.0;
+        L.w2[i] = 0.0;
+        L.tag[i] = 0;
+        L.count[i] = 0;
+    }
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t wide = 64u >> r.hw;                // ids of a wave's row
+    const uint32_t across = per_row / wide;           // waves side by side in a tile
+    const uint32_t turns = 4u << a.tp.rounds;         // a wave's worth of rays, of the tile
+    const MXR_CONSTANT RunArgs *args =
+        (const MXR_CONSTANT RunArgs *)((const MXR_CONSTANT char *)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(void *));
+    const uint32_t slot0 = det.slot;
+    for (uint32_t t = wave; t < turns; t += kBlock / 64) {
+        const DevInstr *ins = (const DevInstr *)again((const MXR_CONSTANT DevInstr *)insc);
+        const RunArgs &a = *(const RunArgs *)again(args);
+        const TileRange &r = a.tp.r[ri];
+        const uint32_t row = row0 + ((t / across) << r.hw) + lane / wide;
+        const uint64_t col = col0 + (t % across) * wide + lane % wide;
+        const bool in = row < r.rows;
+        const uint64_t at = row_start(r, in ? row : 0);
+        const uint64_t len = in ? row_start(r, row + 1) - at : 0;
+        const bool live = col < len;
+        const uint64_t ray_id = live ? at + col : r.first;  // a lane without a ray holds the range's first, dead
+        const TallyHit hit = run_tallied<EXACT, kWalkRound>(C{}, ins, ray_id, live, a, mu_lds, n_mat, n_ebin);
+        if (!hit.live) continue;
+        bool done = false;
+        if (slots) {
+            const uint32_t slot = ((((hit.iy & ((1u << a.tp.ly) - 1)) << a.tp.lx) | (hit.ix & ((1u << a.tp.lx) - 1))) * ne) + hit.ie;
+            const uint32_t tag = (uint32_t)hit.bin + 1u;
+            const uint32_t held = atomicCAS(L.tag + slot, 0u, tag);
+            if (held == 0u || held == tag) {
+                atomicAdd(L.count + slot, 1u);
+                atomicAdd(L.w + slot, hit.w);
+                atomicAdd(L.w2 + slot, hit.w * hit.w);
+                done = true;
+            }
+        }
+        if (!done) tally_global(a, slot0, hit);
+    }
+    if (slots) {
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < slots; i += kBlock) {
+            const uint32_t tag = L.tag[i];
+            if (tag == 0) continue;
+            atomicAdd(a.tally.count[slot0] + (tag - 1u), (unsigned long long)L.count[i]);
+            atomicAdd(a.tally.sum_w[slot0] + (tag - 1u), L.w[i]);
+            atomicAdd(a.tally.sum_w2[slot0] + (tag - 1u), L.w2[i]);
         }
     }
 }
@@ -752,9 +848,8 @@ __global__ __launch_bounds__(kBlock, BatchWavesHint<C>::value) void k_batch(cons
             for (uint64_t r = r0; r < r1; r += kBlock) {  // every lane takes part
                 const bool live = r + threadIdx.x < r1;
                 const uint64_t ray_id = live ? r + threadIdx.x : r1 - 1;
-                Stream s;
-                s.init(a.seed, ray_id, a.word3);
-                run_tallied<EXACT, kWalkRound>(C{}, ins, s, ray_id, live, a, mu_lds, n_mat, n_ebin);
+                tally_global(a, ins->c[ins->ncomp - 1].slot,
+                             run_tallied<EXACT, kWalkRound>(C{}, ins, ray_id, live, a, mu_lds, n_mat, n_ebin));
             }
         } else {
             for (uint64_t ray_id = r0 + threadIdx.x; ray_id < r1; ray_id += kBlock) {
@@ -809,8 +904,8 @@ __global__ __launch_bounds__(kBlock, BatchWavesHint<C>::value) void k_batch_grid
     Stream s;
     if constexpr (ends_in_absorber(C{})) {
         const uint64_t ray_id = id < a.n ? id : a.n - 1;  // every lane takes part
-        s.init(a.seed, ray_id, a.word3);
-        run_tallied<EXACT, kWalkRound>(C{}, ins, s, ray_id, id < a.n, a, mu_lds, n_mat, n_ebin);
+        tally_global(a, ins->c[ins->ncomp - 1].slot,
+                     run_tallied<EXACT, kWalkRound>(C{}, ins, ray_id, id < a.n, a, mu_lds, n_mat, n_ebin));
     } else {
         if (id >= a.n) return;
         const LedgerLds L{nullptr};
@@ -944,16 +1039,29 @@ template <class C, bool EXACT>
 struct KernelSet {
     static KernelFn get(bool ledger, bool trace) {
         if (trace) return ledger ? k_trace<C, true, true, EXACT> : k_trace<C, false, true, EXACT>;
-        return ledger ? k_trace<C, true, false, EXACT> : k_trace<C, false, false, EXACT>;
+        if (ledger) return k_trace<C, true, false, EXACT>;
+        if constexpr (ends_in_absorber(C{}))
+            return k_image<C, EXACT>;
+        else
+            return k_trace<C, false, false, EXACT>;
     }
     // the plain run kernel compiled for another occupancy (waves per SIMD;
     // 0: the chain's own)
     static KernelFn plain(uint32_t waves) {
-        switch (waves) {
-            case 4: return k_trace<C, false, false, EXACT, 4>;
-            case 6: return k_trace<C, false, false, EXACT, 6>;
-            case 8: return k_trace<C, false, false, EXACT, 8>;
-            default: return k_trace<C, false, false, EXACT>;
+        if constexpr (ends_in_absorber(C{})) {
+            switch (waves) {
+                case 4: return k_image<C, EXACT, 4>;
+                case 6: return k_image<C, EXACT, 6>;
+                case 8: return k_image<C, EXACT, 8>;
+                default: return k_image<C, EXACT>;
+            }
+        } else {
+            switch (waves) {
+                case 4: return k_trace<C, false, false, EXACT, 4>;
+                case 6: return k_trace<C, false, false, EXACT, 6>;
+                case 8: return k_trace<C, false, false, EXACT, 8>;
+                default: return k_trace<C, false, false, EXACT>;
+            }
         }
     }
 };
@@ -1001,13 +1109,20 @@ KernelFn pick_kernel(int recipe, bool ledger, bool trace, bool exact, int mode) 
                          : KernelSet<ChainEdctScatter, false>::get(ledger, trace);
         case kRecipeEdctAimed:
             // plain runs only; ledgers and ray traces take the generic chain
-            if (exact && !ledger && !trace) return k_trace<ChainEdctAimed, false, false, true>;
+            if (exact && !ledger && !trace) return k_image<ChainEdctAimed, true>;
             return exact ? KernelSet<ChainGeneric, true>::get(ledger, trace)
                          : KernelSet<ChainGeneric, false>::get(ledger, trace);
         default:
             return exact ? KernelSet<ChainGeneric, true>::get(ledger, trace)
                          : KernelSet<ChainGeneric, false>::get(ledger, trace);
     }
+}
+
+// whether pick_kernel's choice is an image kernel (launched by tiles)
+bool is_image_kernel(int recipe, bool ledger, bool trace, bool exact, int mode) {
+    if (ledger || trace) return false;
+    if (mode == kModePlain) return recipe == kRecipeEdct || recipe == kRecipeEdctStep || (recipe == kRecipeEdctAimed && exact);
+    return recipe == kRecipeEdct && (mode == kModeProposal || mode == kModeCollect);
 }
 
 // the compacting kernel for plain runs of a chain with a compaction prefix,
@@ -1473,6 +1588,85 @@ void mxr_instrument_destroy(mxr_instrument *ins) {
     delete ins;
 }
 
+// Tiles of a launch of an image kernel over rays [a.first, a.first + a.n).
+// Rounds per tile: as many (at most 16) as leave 16,384 tiles, some 16 to a
+// work-group's place on the chip (of a plain cone's tiles 70 % end at once).
+// A whole run's tiles follow the rows of its stratified ranges; a part of a run
+// is one row.  Rows per tile and per wave make both about square on the
+// monitor: a cell holds c rays, so a wave covers 64 / c cells, `ratio` times
+// as wide as high in a proposal's components.
+static void plan_tiles(RunArgs &a, const DevInstr &d, const PropTable *prop) {
+    TilePlan &tp = a.tp;
+    tp = TilePlan{};
+    const bool whole = a.first == 0 && a.n == a.n_total;
+    const bool steps = d.phantom >= 0 && (d.c[d.phantom].flags & 1u);
+    while (!steps && tp.rounds < 4 && (a.n >> (8 + 14 + tp.rounds + 1)) > 0) ++tp.rounds;
+    auto log2_of = [](double x, uint32_t most) {
+        uint32_t l = 0;
+        while (l < most && x > 1.4142 * (double)(1u << l)) ++l;
+        return l;
+    };
+    auto add = [&](uint64_t first, uint64_t n, uint64_t rows, double ratio) {
+        if (n == 0) return;
+        TileRange &r = tp.r[tp.ranges++];
+        r.first = first;
+        r.n = n;
+        r.rows = (uint32_t)rows;
+        r.q = n / rows;
+        r.rem = (uint32_t)(n % rows);
+        r.r_rows = 1.0 / (double)rows;
+        const double c = (double)n / ((double)rows * (double)rows);
+        uint32_t most = 0;  // at most all rows, and at least 8 ids of a row per wave
+        while (most < 3 && (2ull << most) <= rows) ++most;
+        r.hw = rows > 1 ? log2_of(std::sqrt(64.0 / c * ratio), most) : 0;
+        most = r.hw;
+        while (most < r.hw + 2 + tp.rounds && (2ull << most) <= rows) ++most;
+        r.ht = rows > 1 ? std::max(r.hw, log2_of(std::sqrt((double)(256u << tp.rounds) / c * ratio), most)) : 0;
+        const uint64_t per_row = (256u << tp.rounds) >> r.ht, len = r.q + (r.rem ? 1 : 0);
+        r.cols = (uint32_t)((len + per_row - 1) / per_row);
+        r.r_cols = 1.0 / (double)r.cols;
+        r.tiles = (uint64_t)r.cols * ((rows + (1ull << r.ht) - 1) >> r.ht);
+        tp.tiles += r.tiles;
+    };
+    if (!whole) {
+        add(a.first, a.n, 1, 1.0);
+    } else if (prop) {
+        for (int b = 0; b < 9; ++b) {
+            const uint64_t first = b ? a.pb[b - 1] : 0;
+            add(first, a.pb[b] - first, a.psd[b].G, b ? prop->sigma[b - 1][0] / prop->sigma[b - 1][1] : 1.0);
+        }
+    } else {
+        add(0, a.n, a.G, 1.0);
+        tp.cull = tp.rounds > 0 || steps;
+    }
+    // the private histogram: a window of up to 1024 bins, for monitors whose
+    // bins fit the tags
+    const uint32_t *dims = d.c[d.ncomp - 1].dims;
+    if (tp.rounds > 0 && dims[2] <= 1024 && (uint64_t)dims[0] * dims[1] * dims[2] < ~0u) {
+        tp.lds_ne = dims[2];
+        while ((dims[2] << (tp.lx + tp.ly + 1)) <= 1024) ++(tp.lx > tp.ly ? tp.ly : tp.lx);
+    }
+}
+
+// LDS of an image kernel: the attenuation table and the private histogram.
+static size_t image_lds(const RunArgs &a, const DevInstr &d) {
+    return (size_t)d.n_mat * d.n_ebin * sizeof(double) + (size_t)(a.tp.lds_ne << (a.tp.lx + a.tp.ly)) * 24;
+}
+
+// Launches kernel k over the tiles of a.tp, at most kMaxLaunchGroups at a time.
+static hipError_t launch_tiles(KernelFn k, const DevInstr *dev, RunArgs a, size_t shmem, hipStream_t stream) {
+    for (uint64_t done = 0; done < a.tp.tiles; done += kMaxLaunchGroups) {
+        const uint64_t groups = std::min(a.tp.tiles - done, kMaxLaunchGroups);
+        a.tp.first_tile = done;
+        a.blocks_per_xcd = (uint32_t)((groups + 7) / 8);
+        hipLaunchKernelGGL(k, dim3((unsigned)(a.blocks_per_xcd * 8u)), dim3(kBlock), shmem, stream,
+                           (const MXR_CONSTANT_PARAM DevInstr *)dev, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 static mxr_status launch(mxr_instrument *ins, const RunArgs &base, uint64_t n, bool ledger, bool trace,
                          hipStream_t stream) {
     const bool exact = ins->host.phantom < 0 || ins->host.c[ins->host.phantom].aux[4] != 0.0;
@@ -1483,6 +1677,13 @@ static mxr_status launch(mxr_instrument *ins, const RunArgs &base, uint64_t n, b
     if (plain && ins->shape.occupancy) {
         KernelFn ko = pick_plain(ins->recipe, exact, ins->shape.occupancy);
         if (ko) k = ko;
+    }
+    if (is_image_kernel(ins->recipe, ledger, trace, exact, mode)) {
+        RunArgs a = base;
+        a.xcd_order = plain ? ins->shape.xcd_order : ins->order;
+        plan_tiles(a, ins->host, base.prop ? &ins->prop_host : nullptr);
+        const hipError_t e = launch_tiles(k, ins->dev, a, image_lds(a, ins->host), stream);
+        return e == hipSuccess ? MXR_OK : hip_fail(e, "kernel launch");
     }
     KernelFn kc = (plain && ins->shape.compact) ? pick_compact(ins->recipe) : nullptr;
     size_t shmem = 0;
@@ -1909,7 +2110,8 @@ struct mxr_batch {
     bool exact;
     uint32_t n_jobs;
     uint64_t total_rays, total_cost;
-    std::vector<BatchJob> host_jobs;  // longest-first
+    std::vector<BatchJob> host_jobs;          // longest-first
+    std::vector<const DevInstr *> host_ins;  // their instruments' constants (host)
     BatchJob *dev_jobs;
     unsigned long long *counter;
     size_t shmem;
@@ -2034,8 +2236,17 @@ static mxr_status batch_capture(mxr_batch *b) {
         launch_err = hipEventRecord(b->fork, b->capture_stream);
         for (uint32_t i = 0; launch_err == hipSuccess && i < nb; ++i)
             launch_err = hipStreamWaitEvent(b->branch[i], b->fork, 0);
-        for (uint32_t j = 0; launch_err == hipSuccess && j < b->n_jobs; ++j)
-            launch_err = launch_job(k, b->host_jobs[j].args, b->shmem, b->branch[j % nb]);
+        const bool image = is_image_kernel(b->recipe, false, false, b->exact, kModePlain);
+        for (uint32_t j = 0; launch_err == hipSuccess && j < b->n_jobs; ++j) {
+            RunArgs a = b->host_jobs[j].args;
+            if (image) {
+                const DevInstr &d = *b->host_ins[j];
+                plan_tiles(a, d, nullptr);
+                launch_err = launch_tiles(k, a.ins, a, image_lds(a, d), b->branch[j % nb]);
+            } else {
+                launch_err = launch_job(k, a, b->shmem, b->branch[j % nb]);
+            }
+        }
         for (uint32_t i = 0; launch_err == hipSuccess && i < nb; ++i) {
             launch_err = hipEventRecord(b->join[i], b->branch[i]);
             if (launch_err == hipSuccess) launch_err = hipStreamWaitEvent(b->capture_stream, b->join[i], 0);
@@ -2158,7 +2369,10 @@ mxr_status mxr_batch_create(const mxr_batch_job *jobs, uint32_t n_jobs, const mx
     b->n_jobs = n_jobs;
     b->total_rays = total_rays;
     b->total_cost = total_cost;
-    for (const auto &o : order) b->host_jobs.push_back(hj[o.second]);
+    for (const auto &o : order) {
+        b->host_jobs.push_back(hj[o.second]);
+        b->host_ins.push_back(&jobs[o.second].instrument->host);
+    }
     e = hipDeviceGetAttribute(&b->n_cu, hipDeviceAttributeMultiprocessorCount, cur);
     if (e != hipSuccess || b->n_cu < 1) b->n_cu = 256;
     // one launch per job, one branch, until tuned

@@ -21,6 +21,24 @@
 
 namespace mxr {
 
+// The device's constant address space, for tables that no kernel writes
+// while they are read (in the host pass, where kernel bodies are only
+// parsed, it is the ordinary one).
+#if defined(__HIP_DEVICE_COMPILE__)
+#define MXR_CONSTANT __attribute__((address_space(4)))
+#else
+#define MXR_CONSTANT
+#endif
+
+// The same address, which the compiler takes for another: the constants behind
+// it are loaded again where they are used next instead of being held, and
+// spilled into vector lanes, in scalar registers.
+template <class T>
+__device__ __forceinline__ const MXR_CONSTANT T *again(const MXR_CONSTANT T *p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 constexpr double kHc = 12.398419843320026;  // keV * Angstrom (CODATA 2018)
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kTwoPi = 2.0 * 3.14159265358979323846;
@@ -105,6 +123,31 @@ struct StratDiv {
     double rn, rG, rG2, f0, f1;
 };
 
+// Rays [first, first + n) of a tiled launch, laid out in `rows` rows of
+// consecutive ids: row r begins at first + ceil(r n / rows).  The rows of a
+// stratified range are its rows of cells, so the rays at one place of
+// neighbouring rows leave in neighbouring directions.  A tile is 2^ht rows of
+// (tile rays >> ht) ids each; the tiles run along the rows first, `cols` to a
+// block of rows.  A wave takes 2^hw rows of 64 >> hw ids at a time.
+struct TileRange {
+    uint64_t first, n, q, tiles;  // q = n / rows; tiles of this range
+    uint32_t rows, rem;           // rem = n mod rows
+    uint32_t cols, ht, hw, pad;
+    double r_rows, r_cols;        // 1 / rows, 1 / cols, rounded
+};
+
+// The tiles of a launch of the image kernels: 256 << rounds rays each, the
+// ranges' tiles one after the other.
+struct TilePlan {
+    uint64_t first_tile, tiles;  // of this launch, of the whole run
+    uint32_t rounds, ranges;
+    // the work-group's private histogram: 2^lx x 2^ly pixels of lds_ne energy
+    // bins (0: none)
+    uint32_t lx, ly, lds_ne;
+    uint32_t cull;               // the one range is a whole stratified cone: tiles that miss the monitor end at once
+    TileRange r[9];
+};
+
 struct RunArgs {
     const DevInstr *ins;
     uint64_t first, n, n_total, seed;
@@ -126,6 +169,7 @@ struct RunArgs {
     StratDiv psd[9];
     double pc[9];
     HitSink hits;  // hit-collecting runs
+    TilePlan tp;   // tiled launches (the image kernels)
 };
 
 // ------------------------------------------------------------- Philox ----
@@ -648,8 +692,28 @@ struct PhantomGeo {
     double blo[3], bhi[3];
     uint32_t bg;
     bool box;
-    const uint8_t *bricks;  // material of each 4^3-voxel brick, or 255 if it holds several (plain runs)
 };
+
+__device__ __forceinline__ PhantomGeo phantom_geo(const DevComp &c) {
+    PhantomGeo g;
+    g.vol = (const uint8_t *)c.data0;
+    g.n[0] = (int)c.dims[0];
+    g.n[1] = (int)c.dims[1];
+    g.n[2] = (int)c.dims[2];
+    g.v = c.par[0];
+    g.rv = c.aux[6];
+    g.corner[0] = c.aux[0];
+    g.corner[1] = c.aux[1];
+    g.corner[2] = c.aux[2];
+    g.nvox = (uint32_t)c.n0;
+    for (int i = 0; i < 3; ++i) {
+        g.blo[i] = c.aux[8 + i];
+        g.bhi[i] = c.aux[11 + i];
+    }
+    g.bg = (uint32_t)c.aux[14];
+    g.box = c.aux[15] != 0.0;
+    return g;
+}
 
 // The loaded byte goes through an empty asm so that it stays a plain 32-bit
 // value: the compiler otherwise narrows the walk's materials to 16 bits and
@@ -1096,21 +1160,42 @@ constexpr int kMixed = 255, kNoLayer = 254;  // codes of a layer beside its one 
 constexpr int kBrick = 4;                    // voxels along a brick's edge
 constexpr int kStretchRound = 4;  // crossings per round of a stretch's walk
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_min(float x) {
-    return fminf(x, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, 0xf, 0xf, false)));
+// The least over the wave of each of eight values, in scalar registers.
+// row_shr 1, 2, 4, 8 leave a row's least value in its last lane, row_bcast 15
+// and 31 carry it on to lane 63; a lane without a source lane keeps its own.
+// One instruction a step (the compiler's form of update_dpp and fminf takes
+// four); eight chains side by side keep the two wait states between a write
+// and a DPP read.
+#define MXR_MIN8(step)                                 \
+    "v_min_f32_dpp %0, %0, %0 " step "\n\t"            \
+    "v_min_f32_dpp %1, %1, %1 " step "\n\t"            \
+    "v_min_f32_dpp %2, %2, %2 " step "\n\t"            \
+    "v_min_f32_dpp %3, %3, %3 " step "\n\t"            \
+    "v_min_f32_dpp %4, %4, %4 " step "\n\t"            \
+    "v_min_f32_dpp %5, %5, %5 " step "\n\t"            \
+    "v_min_f32_dpp %6, %6, %6 " step "\n\t"            \
+    "v_min_f32_dpp %7, %7, %7 " step "\n\t"
+__device__ __forceinline__ void wave_min8(float x[8]) {
+    asm("s_nop 1\n\t" MXR_MIN8("row_shr:1 row_mask:0xf bank_mask:0xf") MXR_MIN8("row_shr:2 row_mask:0xf bank_mask:0xf")
+            MXR_MIN8("row_shr:4 row_mask:0xf bank_mask:0xf") MXR_MIN8("row_shr:8 row_mask:0xf bank_mask:0xf")
+                MXR_MIN8("row_bcast:15 row_mask:0xf bank_mask:0xf") MXR_MIN8("row_bcast:31 row_mask:0xf bank_mask:0xf")
+        "s_nop 1"
+        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[i]), 63));
 }
-// The least of the lanes' values, in a scalar register: row_shr 1, 2, 4, 8
-// leave a row's least value in its last lane, row_bcast 15 and 31 carry it
-// on to lane 63.
-__device__ __forceinline__ float wave_min(float x) {
-    x = dpp_min<0x111>(x);
-    x = dpp_min<0x112>(x);
-    x = dpp_min<0x114>(x);
-    x = dpp_min<0x118>(x);
-    x = dpp_min<0x142>(x);
-    x = dpp_min<0x143>(x);
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+#undef MXR_MIN8
+
+// floor(x) as an integer, the lesser of two floats: one instruction each.
+__device__ __forceinline__ int floor_i32(float x) {
+    int r;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+__device__ __forceinline__ float min_f32(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 
 // Open material run of a path: material m (attenuation mu, read when the run
@@ -1132,14 +1217,23 @@ __device__ __forceinline__ void turn_run(OpenRun &run, double t, double a_out, u
     run.mu = mu_row[m];
 }
 
-// One axis of a path across the volume, in the role of D, A or B.  The
-// corner, voxel count and stride are the wave's, start, direction and
-// reciprocal the lane's (direction 0: reciprocal 0).
+// One axis of a path across the volume, in the role of D, A or B: the
+// lane's start, direction and reciprocal (direction 0: reciprocal 0).
 struct Role {
-    double c;
-    int n, str;
     double q, d, inv;
 };
+// Its constants, the wave's: corner, voxel count and strides of the voxels
+// and of the bricks.
+struct RoleAxis {
+    double c;
+    int n, str, brick;
+};
+__device__ __forceinline__ RoleAxis role_axis(const MXR_CONSTANT DevComp *ph, int i) {
+    const int nx = (int)ph->dims[0], ny = (int)ph->dims[1], nz = (int)ph->dims[2];
+    const int bx = (nx + kBrick - 1) / kBrick, by = (ny + kBrick - 1) / kBrick;
+    return {pick3(i, ph->aux[0], ph->aux[1], ph->aux[2]), pick3(i, nx, ny, nz), pick3(i, 1, nx, nx * ny),
+            pick3(i, 1, bx, bx * by)};
+}
 
 // State of an axis at alpha as: the next plane ahead (coordinate mirrored by
 // the sign of the direction), its index, and the voxel before it.  The plane
@@ -1149,21 +1243,20 @@ struct RoleStep {
     double P, iv, nq, c;
     int k, idx, off;
 };
-__device__ __forceinline__ RoleStep role_at(const Role &r, const PhantomGeo &g, double as) {
+__device__ __forceinline__ RoleStep role_at(const Role &r, const RoleAxis &x, double v, double rv, double as) {
     RoleStep s;
     const bool fwd = r.d > 0.0;
-    const double f = floor(((r.q + as * r.d) - r.c) * g.rv);
-    const double cf = ceil(((r.q + as * r.d) - r.c) * g.rv);
+    const double f = ((r.q + as * r.d) - x.c) * rv;
     // forward: voxel floor(f), plane one above it; backward: plane ceil(f) - 1,
     // the voxel above that plane; along the axis: voxel floor(f), no plane
-    int v = (int)fmin(fmax(r.d < 0.0 ? cf - 1.0 : f, 0.0), (double)(r.n - 1));
-    s.idx = v;
-    s.k = fwd ? v + 1 : -v;
-    s.c = fwd ? r.c : -r.c;
+    const double g = r.d < 0.0 ? ceil(f) - 1.0 : floor(f);
+    s.idx = (int)min_f64(max_f64(g, 0.0), (double)(x.n - 1));
+    s.k = fwd ? s.idx + 1 : -s.idx;
+    s.c = fwd ? x.c : -x.c;
     s.iv = fwd ? r.inv : -r.inv;
     s.nq = r.d == 0.0 ? kInf : -(r.q * r.inv);
-    s.P = s.c + (double)s.k * g.v;
-    s.off = r.d == 0.0 ? 0 : (fwd ? r.str : -r.str);
+    s.P = s.c + (double)s.k * v;
+    s.off = r.d == 0.0 ? 0 : (fwd ? x.str : -x.str);
     return s;
 }
 
@@ -1173,24 +1266,25 @@ __device__ __forceinline__ RoleStep role_at(const Role &r, const PhantomGeo &g, 
 // events of the path all the same; the next stretch or change sees them again
 // as runs of no length (turn_run never sets a run back).
 template <bool EXACT, int K>
-__device__ __forceinline__ void stretch_walk(const PhantomGeo &g, const Role &D, const Role &A, const Role &B,
-                                             bool back, int layer, bool late, double as, double ae, double a_out,
-                                             OpenRun &run, const double *__restrict__ mu_row) {
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)g.vol, (short)0, (int)g.nvox, 0x00020000);
-    const double v = g.v;
-    const RoleStep a = role_at(A, g, as), b = role_at(B, g, as);
-    if (late) layer = role_at(D, g, as).idx;
-    const double cD = back ? -D.c : D.c, iD = back ? -D.inv : D.inv, nD = -(D.q * D.inv);
+__device__ __forceinline__ void stretch_walk(const MXR_CONSTANT DevComp *ph, int axD, const Role &D, const Role &A,
+                                             const Role &B, bool back, int layer, bool late, double as, double ae,
+                                             double a_out, OpenRun &run, const double *__restrict__ mu_row) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)ph->data0, (short)0, (int)ph->n0, 0x00020000);
+    const RoleAxis xD = role_axis(ph, axD), xA = role_axis(ph, axD == 0 ? 1 : 0), xB = role_axis(ph, axD == 2 ? 1 : 2);
+    const double v = ph->par[0], rv = ph->aux[6];
+    const RoleStep a = role_at(A, xA, v, rv, as), b = role_at(B, xB, v, rv, as);
+    if (late) layer = role_at(D, xD, v, rv, as).idx;
+    const double cD = back ? -xD.c : xD.c, iD = back ? -D.inv : D.inv, nD = -(D.q * D.inv);
     int kD = back ? -layer : layer + 1, kA = a.k, kB = b.k;
     double PD = cD + (double)kD * v, PA = a.P, PB = b.P;
     double aD = plane_alpha<true>(PD, 0.0, iD, nD);
     double aA = plane_alpha<true>(PA, 0.0, a.iv, a.nq), aB = plane_alpha<true>(PB, 0.0, b.iv, b.nq);
     double mAB = min_f64(aA, aB);
-    const int oD = back ? -D.str : D.str, dA = a.off - oD, dB = b.off - oD;
-    uint32_t off = (uint32_t)(layer * D.str + a.idx * A.str + b.idx * B.str);
+    const int oD = back ? -xD.str : xD.str, dA = a.off - oD, dB = b.off - oD;
+    uint32_t off = (uint32_t)(layer * xD.str + a.idx * xA.str + b.idx * xB.str);
     uint32_t m0 = load_voxel(rs, off);
     bool first = true;
-    const int max_rounds = (g.n[0] + g.n[1] + g.n[2] + 3) / K + 2;
+    const int max_rounds = (xD.n + xA.n + xB.n + 3) / K + 2;
     for (int round = 0; round < max_rounds; ++round) {
         uint32_t o[K];
         double t[K];
@@ -1269,36 +1363,36 @@ __device__ __forceinline__ int footprint_code(__amdgpu_buffer_rsrc_t rs, uint32_
     return diff == 0 ? (int)m00 : kMixed;
 }
 
-// tau of every lane with in = true (its path enters the volume at a_vol and
-// leaves it at a_out, inv = 1 / dl); all 64 lanes of the wave call it together.
+// tau of every lane with in = true (its path enters the volume of the phantom
+// ph at a_vol and leaves it at a_out, inv = 1 / dl); all 64 lanes of the wave
+// call it together.
 template <bool EXACT>
-__device__ __forceinline__ double bundle_tau(const PhantomGeo &g, const double q[3], const double dl[3],
-                                             const double inv[3], double a_vol, double a_out, bool in,
-                                             const double *__restrict__ mu_row) {
-    const int nbx = (g.n[0] + kBrick - 1) / kBrick, nby = (g.n[1] + kBrick - 1) / kBrick;
-    const int nbz = (g.n[2] + kBrick - 1) / kBrick;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)g.vol, (short)0, (int)g.nvox, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void *)g.bricks, (short)0, nbx * nby * nbz, 0x00020000);
+__device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, const MXR_CONSTANT uint8_t *bricks,
+                                             const double q[3], const double dl[3], const double inv[3], double a_vol,
+                                             double a_out, bool in, const double *__restrict__ mu_row) {
     const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     // the dominant axis, as in siddon_tau, and its direction
     const double ax = fabs(dl[0]), ay = fabs(dl[1]), az = fabs(dl[2]);
     const int ownD = (ax >= ay && ax >= az) ? 0 : (ay >= az ? 1 : 2);
     const int own = 2 * ownD + (pick3(ownD, dl[0], dl[1], dl[2]) < 0.0);
-    OpenRun run{g.bg, mu_row[g.bg], a_vol, 0.0};
+    const MXR_CONSTANT DevComp *const p0 = again(comp);
+    const uint32_t bg = (uint32_t)p0->aux[14];
+    OpenRun run{bg, mu_row[bg], a_vol, 0.0};
     // the path's part inside the occupied box, as in siddon_tau; outside it
     // the run of background stays open
     double a_box = a_vol, z_box = a_out;
-    bool hit = in && g.box;
+    bool hit = in && p0->aux[15] != 0.0;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
+        const double lo = p0->aux[8 + i], hi = p0->aux[11 + i];
         const double nq = -(q[i] * inv[i]);
-        const double b0 = fma(g.blo[i], inv[i], nq), b1 = fma(g.bhi[i], inv[i], nq);
+        const double b0 = fma(lo, inv[i], nq), b1 = fma(hi, inv[i], nq);
         if (dl[i] != 0.0) {
-            a_box = fmax(a_box, fmin(b0, b1));
-            z_box = fmin(z_box, fmax(b0, b1));
+            a_box = max_f64(a_box, min_f64(b0, b1));
+            z_box = min_f64(z_box, max_f64(b0, b1));
         } else {
-            const double idx = fmin(fmax(floor((q[i] - g.corner[i]) / g.v), 0.0), (double)(g.n[i] - 1));
-            hit = hit && idx >= rint((g.blo[i] - g.corner[i]) * g.rv) && idx < rint((g.bhi[i] - g.corner[i]) * g.rv);
+            const double c = p0->aux[i], idx = fmin(fmax(floor((q[i] - c) / p0->par[0]), 0.0), (double)((int)p0->dims[i] - 1));
+            hit = hit && idx >= rint((lo - c) * p0->aux[6]) && idx < rint((hi - c) * p0->aux[6]);
         }
     }
     hit = hit && z_box > a_box;
@@ -1311,60 +1405,69 @@ __device__ __forceinline__ double bundle_tau(const PhantomGeo &g, const double q
         live &= ~__builtin_amdgcn_ballot_w64(part);
         const int iD = side >> 1, iA = iD == 0 ? 1 : 0, iB = iD == 2 ? 1 : 2;
         const bool back = (side & 1) != 0;
-        const int sx = 1, sy = g.n[0], sz = g.n[0] * g.n[1];
         auto role = [&](int i) {
-            return Role{pick3(i, g.corner[0], g.corner[1], g.corner[2]), pick3(i, g.n[0], g.n[1], g.n[2]),
-                        pick3(i, sx, sy, sz), pick3(i, q[0], q[1], q[2]), pick3(i, dl[0], dl[1], dl[2]),
-                        pick3(i, inv[0], inv[1], inv[2])};
+            return Role{pick3(i, q[0], q[1], q[2]), pick3(i, dl[0], dl[1], dl[2]), pick3(i, inv[0], inv[1], inv[2])};
         };
         const Role D = role(iD), A = role(iA), B = role(iB);
-        const int bstrD = pick3(iD, 1, nbx, nbx * nby), bstrA = pick3(iA, 1, nbx, nbx * nby);
-        const int bstrB = pick3(iB, 1, nbx, nbx * nby);
+        const MXR_CONSTANT DevComp *const ph = again(comp);
+        const RoleAxis xD = role_axis(ph, iD);
+        const double v = ph->par[0];
         // layers of bricks along D that hold the occupied box, and their
         // outer planes
-        const int Lo = __builtin_amdgcn_readfirstlane((int)rint((pick3(iD, g.blo[0], g.blo[1], g.blo[2]) - D.c) * g.rv));
-        const int Hi = __builtin_amdgcn_readfirstlane((int)rint((pick3(iD, g.bhi[0], g.bhi[1], g.bhi[2]) - D.c) * g.rv));
+        const double rv = ph->aux[6];
+        const int Lo = __builtin_amdgcn_readfirstlane((int)rint((pick3(iD, ph->aux[8], ph->aux[9], ph->aux[10]) - xD.c) * rv));
+        const int Hi = __builtin_amdgcn_readfirstlane((int)rint((pick3(iD, ph->aux[11], ph->aux[12], ph->aux[13]) - xD.c) * rv));
         const int bLo = Lo / kBrick, bHi = (Hi + kBrick - 1) / kBrick, NB = bHi - bLo;
-        const int P0 = bLo * kBrick, P1 = bHi * kBrick < D.n ? bHi * kBrick : D.n;
+        const int P0 = bLo * kBrick, P1 = bHi * kBrick < xD.n ? bHi * kBrick : xD.n;
         const double nD = -(D.q * D.inv);
-        auto alpha_of = [&](int plane) { return fma(D.c + (double)plane * g.v, D.inv, nD); };
-        const double e0 = alpha_of(P0), e1 = alpha_of(P1);
-        const float xA0 = (float)(((A.q - A.c) + e0 * A.d) * g.rv), xA1 = (float)(((A.q - A.c) + e1 * A.d) * g.rv);
-        const float xB0 = (float)(((B.q - B.c) + e0 * B.d) * g.rv), xB1 = (float)(((B.q - B.c) + e1 * B.d) * g.rv);
-        const float big = 1e30f, perL = 1.0f / (float)(P1 - P0);
-        const float A0 = wave_min(part ? xA0 : big), A1 = (wave_min(part ? xA1 : big) - A0) * perL;
-        const float B0 = wave_min(part ? xB0 : big), B1 = (wave_min(part ? xB1 : big) - B0) * perL;
-        const float mA0 = wave_min(part ? -xA0 : big), mA1 = (wave_min(part ? -xA1 : big) - mA0) * perL;
-        const float mB0 = wave_min(part ? -xB0 : big), mB1 = (wave_min(part ? -xB1 : big) - mB0) * perL;
+        auto alpha_of = [&](int plane) { return fma(xD.c + (double)plane * v, D.inv, nD); };
+        float m[8];
+        {
+            const double e0 = alpha_of(P0), e1 = alpha_of(P1);
+            const double cA = pick3(iA, ph->aux[0], ph->aux[1], ph->aux[2]), cB = pick3(iB, ph->aux[0], ph->aux[1], ph->aux[2]);
+            const float xA0 = (float)(((A.q - cA) + e0 * A.d) * rv), xA1 = (float)(((A.q - cA) + e1 * A.d) * rv);
+            const float xB0 = (float)(((B.q - cB) + e0 * B.d) * rv), xB1 = (float)(((B.q - cB) + e1 * B.d) * rv);
+            const float big = 1e30f;
+            m[0] = part ? xA0 : big, m[1] = part ? xA1 : big, m[2] = part ? xB0 : big, m[3] = part ? xB1 : big;
+            m[4] = part ? -xA0 : big, m[5] = part ? -xA1 : big, m[6] = part ? -xB0 : big, m[7] = part ? -xB1 : big;
+        }
+        wave_min8(m);
+        const float perL = __builtin_amdgcn_rcpf((float)(P1 - P0));
+        const float A0 = m[0], A1 = (m[1] - A0) * perL, B0 = m[2], B1 = (m[3] - B0) * perL;
+        const float mA0 = m[4], mA1 = (m[5] - mA0) * perL, mB0 = m[6], mB1 = (m[7] - mB0) * perL;
         // a bundle that stays wide, one in few layers, or one in a volume too
         // long for the bounds' precision walks all layers as one stretch
-        const bool narrow = Hi - Lo >= kBundleLayers && g.n[0] <= kBundleDim && g.n[1] <= kBundleDim && g.n[2] <= kBundleDim &&
-                            fminf(-mA0 - A0, -mA0 - A0 - (mA1 + A1) * (float)(P1 - P0)) < kBundleNarrow &&
-                            fminf(-mB0 - B0, -mB0 - B0 - (mB1 + B1) * (float)(P1 - P0)) < kBundleNarrow;
+        const bool narrow = Hi - Lo >= kBundleLayers && (int)ph->dims[0] <= kBundleDim && (int)ph->dims[1] <= kBundleDim &&
+                            (int)ph->dims[2] <= kBundleDim && fminf(-m[4] - m[0], -m[5] - m[1]) < kBundleNarrow &&
+                            fminf(-m[6] - m[2], -m[7] - m[3]) < kBundleNarrow;
         // voxels [a0, a1] x [b0, b1] that the bundle covers between two planes
         int a0, a1, b0, b1;
-        auto footprint = [&](int pa, int pb) {
+        auto footprint = [&](int pa, int pb, int nA, int nB) {
             const float fa = (float)(pa - P0), fb = (float)(pb - P0);
-            a0 = clamp0_i32((int)floorf(fminf(A0 + fa * A1, A0 + fb * A1) - kBundleSlack), A.n - 1);
-            a1 = clamp0_i32((int)floorf(kBundleSlack - fminf(mA0 + fa * mA1, mA0 + fb * mA1)), A.n - 1);
-            b0 = clamp0_i32((int)floorf(fminf(B0 + fa * B1, B0 + fb * B1) - kBundleSlack), B.n - 1);
-            b1 = clamp0_i32((int)floorf(kBundleSlack - fminf(mB0 + fa * mB1, mB0 + fb * mB1)), B.n - 1);
+            a0 = clamp0_i32(floor_i32(min_f32(fmaf(fa, A1, A0), fmaf(fb, A1, A0)) - kBundleSlack), nA - 1);
+            a1 = clamp0_i32(floor_i32(kBundleSlack - min_f32(fmaf(fa, mA1, mA0), fmaf(fb, mA1, mA0))), nA - 1);
+            b0 = clamp0_i32(floor_i32(min_f32(fmaf(fa, B1, B0), fmaf(fb, B1, B0)) - kBundleSlack), nB - 1);
+            b1 = clamp0_i32(floor_i32(kBundleSlack - min_f32(fmaf(fa, mB1, mB0), fmaf(fb, mB1, mB0))), nB - 1);
         };
         // the material every ray is in, or kMixed, and the first plane of the
         // open stretch of mixed layers
-        int prev = narrow ? (int)g.bg : kMixed, open = narrow ? -1 : (back ? P1 : P0);
+        int prev = narrow ? (int)bg : kMixed, open = narrow ? -1 : (back ? P1 : P0);
         for (int base = narrow ? 0 : NB & ~63; base <= NB; base += 64) {
             // the layers of bricks, in travel order; behind the last one the
             // background
             const int t = base + lane;
-            int code = (int)g.bg;
+            int code = (int)bg;
             const int bi = back ? bHi - 1 - t : bLo + t;
             if (narrow && t < NB) {
+                const MXR_CONSTANT DevComp *const ph = again(comp);
+                const RoleAxis xA = role_axis(ph, iA), xB = role_axis(ph, iB);
+                const int all = role_axis(ph, 2).brick * (((int)ph->dims[2] + kBrick - 1) / kBrick);
+                const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void *)bricks, (short)0, all, 0x00020000);
                 const int pa = bi * kBrick;
-                footprint(pa, pa + kBrick < D.n ? pa + kBrick : D.n);
+                footprint(pa, pa + kBrick < xD.n ? pa + kBrick : xD.n, xA.n, xB.n);
                 a0 /= kBrick, a1 /= kBrick, b0 /= kBrick, b1 /= kBrick;
-                code = footprint_code<kBrickWide>(rb, (uint32_t)(bi * bstrD + a0 * bstrA + b0 * bstrB), a1 - a0, b1 - b0,
-                                                  bstrA, bstrB);
+                code = footprint_code<kBrickWide>(rb, (uint32_t)(bi * xD.brick + a0 * xA.brick + b0 * xB.brick), a1 - a0,
+                                                  b1 - b0, xA.brick, xB.brick);
             }
             const int before = __builtin_amdgcn_update_dpp(prev, code, 0x138, 0xf, 0xf, false);  // wave_shr 1
             const uint64_t mixed = __builtin_amdgcn_ballot_w64(code == kMixed);
@@ -1385,7 +1488,7 @@ __device__ __forceinline__ double bundle_tau(const PhantomGeo &g, const double q
                     const int u = __builtin_ctz(sub);
                     sub &= sub - 1;
                     c = __builtin_amdgcn_readlane(fine, shift + u);
-                    const int pb = at * kBrick + kBrick < D.n ? at * kBrick + kBrick : D.n;
+                    const int pb = at * kBrick + kBrick < xD.n ? at * kBrick + kBrick : xD.n;
                     plane = back ? pb - u : at * kBrick + u;
                     if (c == kNoLayer) continue;
                 } else {
@@ -1401,14 +1504,18 @@ __device__ __forceinline__ double bundle_tau(const PhantomGeo &g, const double q
                             const int lb = __builtin_amdgcn_ds_bpermute(4 * kk, nth);
                             const int lt = back ? bHi - 1 - lb : lb - bLo;
                             const int last = __builtin_amdgcn_ds_bpermute(4 * (lt - base), before);
-                            const int pb = lb * kBrick + kBrick < D.n ? lb * kBrick + kBrick : D.n;
+                            const int pb = lb * kBrick + kBrick < xD.n ? lb * kBrick + kBrick : xD.n;
                             const int layer = back ? pb - 1 - u : lb * kBrick + u;
                             const int carry = __builtin_amdgcn_readlane(fine, 63);
                             fine = kNoLayer;
                             if (kk < count && layer >= lb * kBrick && layer < pb) {
-                                footprint(layer, layer + 1);
-                                fine = footprint_code<kBundleWide>(rs, (uint32_t)(layer * D.str + a0 * A.str + b0 * B.str),
-                                                                   a1 - a0, b1 - b0, A.str, B.str);
+                                const MXR_CONSTANT DevComp *const ph = again(comp);
+                                const RoleAxis xA = role_axis(ph, iA), xB = role_axis(ph, iB);
+                                const __amdgpu_buffer_rsrc_t rs =
+                                    __builtin_amdgcn_make_buffer_rsrc((void *)ph->data0, (short)0, (int)ph->n0, 0x00020000);
+                                footprint(layer, layer + 1, xA.n, xB.n);
+                                fine = footprint_code<kBundleWide>(rs, (uint32_t)(layer * xD.str + a0 * xA.str + b0 * xB.str),
+                                                                   a1 - a0, b1 - b0, xA.str, xB.str);
                             }
                             int ahead = __builtin_amdgcn_update_dpp(carry, fine, 0x138, 0xf, 0xf, false);  // wave_shr 1
                             if (u == 0 && last != kMixed) ahead = last;
@@ -1421,7 +1528,7 @@ __device__ __forceinline__ double bundle_tau(const PhantomGeo &g, const double q
                     }
                     c = __builtin_amdgcn_readlane(code, b);
                     ended = base + b == NB;
-                    plane = ended ? (back ? P0 : P1) : (back ? (at * kBrick + kBrick < D.n ? at * kBrick + kBrick : D.n) : at * kBrick);
+                    plane = ended ? (back ? P0 : P1) : (back ? (at * kBrick + kBrick < xD.n ? at * kBrick + kBrick : xD.n) : at * kBrick);
                 }
                 if (c == kMixed) {
                     open = open < 0 ? plane : open;
@@ -1430,10 +1537,10 @@ __device__ __forceinline__ double bundle_tau(const PhantomGeo &g, const double q
                 }
                 if (open >= 0) {
                     // walk the stretch of mixed layers that ends here
-                    const double a0 = alpha_of(open), as = fmax(a0, a_box), ae = fmin(alpha_of(plane), z_box);
+                    const double a0 = alpha_of(open), as = max_f64(a0, a_box), ae = min_f64(alpha_of(plane), z_box);
                     if (part && ae > as)
-                        stretch_walk<EXACT, kStretchRound>(g, D, A, B, back, back ? open - 1 : open, as > a0, as, ae, a_out,
-                                                           run, mu_row);
+                        stretch_walk<EXACT, kStretchRound>(again(comp), iD, D, A, B, back, back ? open - 1 : open, as > a0, as,
+                                                           ae, a_out, run, mu_row);
                     open = -1;
                 }
                 if (c != prev) {
@@ -1952,16 +2059,56 @@ __device__ __forceinline__ int64_t bin_of(double x, double lo, double scale, uin
     return (int64_t)f;
 }
 
-// Pixel iy nx + ix in which a ray reaches the monitor's plane, -1 if it
-// misses the pixels or cannot reach the plane, and the energy (or wavelength)
-// bin: comp_detector in two parts, on the same numbers.
-__device__ __forceinline__ int64_t detector_pixel(const DevComp &c, const Ray &ray) {
+// Pixel (ix, iy) in which a ray reaches the monitor's plane (false: it misses
+// the pixels or cannot reach the plane), and the energy (or wavelength) bin:
+// comp_detector in two parts, on the same numbers.
+__device__ __forceinline__ bool detector_pixel(const DevComp &c, const Ray &ray, uint32_t &ix, uint32_t &iy) {
     double q[3], dl[3];
     to_local(c, ray, q, dl);
-    if (!plane_z0(q, dl)) return -1;
-    const int64_t ix = bin_of(q[0], c.par[0], c.aux[0], c.dims[0]);
-    const int64_t iy = bin_of(q[1], c.par[2], c.aux[1], c.dims[1]);
-    return ix >= 0 && iy >= 0 ? iy * (int64_t)c.dims[0] + ix : -1;
+    if (!plane_z0(q, dl)) return false;
+    const int64_t bx = bin_of(q[0], c.par[0], c.aux[0], c.dims[0]);
+    const int64_t by = bin_of(q[1], c.par[2], c.aux[1], c.dims[1]);
+    ix = (uint32_t)bx;
+    iy = (uint32_t)by;
+    return bx >= 0 && by >= 0;
+}
+
+// Whether every ray of the cone-beam source src whose place (ca, cb) in the
+// source's square lies within (ha, hb) of (ca0, cb0) misses the monitor's
+// pixels (no component between them deflects).  The concentric map moves a
+// point by at most 1.4 times what its argument moves (its Jacobian's largest
+// singular value is 1.383), the map of the disk onto the cone by at most
+// 2 s / cos(alpha/2), s = sin(alpha/2), and a rotation's rows bound the rest;
+// the rays' places on the plane then lie in a box around the middle one's.
+__device__ __forceinline__ bool bundle_misses(const DevComp &src, const DevComp &det, double ca0, double cb0, double ha,
+                                              double hb) {
+    double rad, sa, cs;
+    concentric(ca0, cb0, rad, sa, cs);
+    const double s = src.aux[0], c2 = 1.0 - s * s;
+    if (!(c2 > 1e-6)) return false;
+    const double sh = fabs(rad) * s, k = 2.0 * s * sqrt(1.0 - sh * sh);
+    const double dir[3] = {k * (rad * cs), k * (rad * sa), 1.0 - 2.0 * (sh * sh)};
+    const double eps = (2.0 * s / sqrt(c2)) * (1.4 * sqrt(ha * ha + hb * hb)) + 1e-12;
+    Ray ray;
+    from_origin(src, dir, ray);
+    double q[3], dl[3], err[3];
+    to_local(det, ray, q, dl);
+    double src_norm = 0.0;
+    for (int i = 0; i < 9; ++i) src_norm = src_norm + src.rot[i] * src.rot[i];
+    for (int i = 0; i < 3; ++i) {
+        const double *R = det.rot + 3 * i;
+        err[i] = sqrt((R[0] * R[0] + R[1] * R[1] + R[2] * R[2]) * src_norm) * eps;
+    }
+    if (dl[2] + err[2] <= 0.0 || q[2] > 0.0) return true;  // none reaches the plane moving forward
+    const double low = dl[2] - err[2];
+    if (!(low > 0.0)) return false;
+    for (int i = 0; i < 2; ++i) {
+        const double ratio = dl[i] / dl[2];
+        const double off = fabs(q[2]) * ((err[i] + fabs(ratio) * err[2]) / low);
+        const double x = q[i] - q[2] * ratio, slack = off + 1e-9 * (fabs(q[i]) + fabs(x) + off);
+        if (x + slack < det.par[2 * i] || x - slack > det.par[2 * i + 1]) return true;
+    }
+    return false;
 }
 __device__ __forceinline__ int64_t detector_energy_bin(const DevComp &c, double E) {
     return bin_of((c.flags & 1u) ? kHc / E : E, c.par[4], c.aux[2], c.dims[2]);
