@@ -412,11 +412,11 @@ mxr_status mxr_collect(mxr_instrument *ins, uint64_t first_ray, uint64_t n_rays,
  * mxr_mlp_workspace_layout; row-major, row stride = the row width):
  * X context (n x 6 bf16), Z1 / H1 (n x 128 f32 / bf16), Z2 / H2, O (n x 56
  * f32), DO / DOH gradient of O (f32 / bf16), DZ2 / DZ2H, DZ1 / DZ1H
- * gradients of the pre-activations, PARTIAL per-split gradient partials,
+ * gradients of the pre-activations, PARTIAL per-work-group gradient partials,
  * Y (n x 3 f64) and W (n f64) gathered targets and weights, ROWLOSS (n f64),
  * SCALARS (reduction scratch), WT (the weight matrices transposed, bf16,
  * out x in row-major, at the parameter offsets of W1, W2, W3), COLS
- * (per-tile column sums for the bias gradients). */
+ * (per-work-group losses). */
 #define MXR_MLP_WS_X 0
 #define MXR_MLP_WS_Z1 1
 #define MXR_MLP_WS_H1 2
@@ -460,21 +460,16 @@ mxr_status mxr_mlp_workspace_layout(uint64_t batch, uint64_t *offsets);
 mxr_status mxr_mlp_to_bf16(const float *x, uint64_t n, uint16_t *y, void *hip_stream);
 
 /* Network outputs o (n x 56 f32) of contexts ctx (n x 6 f32) under the
- * bfloat16 parameters w (the forward of the network section above); the layer values stay in ws (ws_bytes >=
- * mxr_mlp_workspace_bytes(n)).  Errors: MXR_E_INVALID, MXR_E_HIP. */
+ * bfloat16 parameters w (the forward of the network section above); the
+ * layer values are left in ws (ws_bytes >= mxr_mlp_workspace_bytes(n)).  Errors: MXR_E_INVALID, MXR_E_HIP. */
 mxr_status mxr_mlp_forward(const uint16_t *w, const float *ctx, uint64_t n, float *out, void *ws, uint64_t ws_bytes,
                            void *hip_stream);
 
 /* mxr_mlp_forward for callers that cannot allocate (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): no workspace
- * argument and no allocation; the layer values live in a static device array
- * of 8 MiB that the library holds on each device it runs on until the
- * process ends (its address is looked up once per device, on the first
- * call).  At most MXR_MLP_NOALLOC_ROWS rows per call.  Calls on one device
- * share that array: calls that overlap on one device (on different streams,
- * or from several host threads) race and must not be issued.  No part of the
- * array needs clearing between calls.  Errors: MXR_E_INVALID (null arrays,
- * n above the limit), MXR_E_HIP. */
+ * argument and no allocation; the layer values stay in registers, so calls
+ * may overlap.  At most MXR_MLP_NOALLOC_ROWS rows per call.  Errors:
+ * MXR_E_INVALID (null arrays, n above the limit), MXR_E_HIP. */
 #define MXR_MLP_NOALLOC_ROWS 4096u
 mxr_status mxr_mlp_forward_noalloc(const uint16_t *w, const float *ctx, uint64_t n, float *out, void *hip_stream);
 
@@ -488,8 +483,8 @@ mxr_status mxr_mlp_mixture(const float *out, uint64_t n, const double lo[3], con
 /* Loss L of the network section above (loss: device double, nullable) and
  * its gradient with respect to the parameters (grad: MXR_MLP_PARAMS f32, overwritten) over n rows
  * (ctx n x 6 f32, y n x 3 f64, omega n f64 >= 0 with a positive sum).
- * The weight gradients are reduced over splits of 1024 rows in a fixed
- * order (deterministic).  Errors: MXR_E_INVALID, MXR_E_HIP. */
+ * The gradients are summed per work-group (passes of 128 rows) and then over
+ * the work-groups in a fixed order (deterministic).  Errors: MXR_E_INVALID, MXR_E_HIP. */
 mxr_status mxr_mlp_loss_grad(const uint16_t *w, const float *ctx, const double *y, const double *omega, uint64_t n,
                              const double lo[3], const double hi[3], float *grad, double *loss, void *ws,
                              uint64_t ws_bytes, void *hip_stream);
