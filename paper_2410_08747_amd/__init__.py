@@ -568,11 +568,9 @@ class Instrument:
         out = []
         for d in self.detectors:
             nb = int(d["nx"]) * int(d["ny"]) * int(d["ne"])
-            out.append({
-                "count": torch.zeros(nb, dtype=torch.int64, device=self.device),
-                "sum_w": torch.zeros(nb, dtype=torch.float64, device=self.device),
-                "sum_w2": torch.zeros(nb, dtype=torch.float64, device=self.device),
-            })
+            # one allocation and one fill for the three
+            count, sum_w, sum_w2 = torch.zeros(3, nb, dtype=torch.float64, device=self.device).unbind(0)
+            out.append({"count": count.view(torch.int64), "sum_w": sum_w, "sum_w2": sum_w2})
         return out
 
     @staticmethod
