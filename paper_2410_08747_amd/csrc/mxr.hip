@@ -240,7 +240,8 @@ struct Chain {};
 // that walk an exact phantom as a bundle hold the scan's and a walk's state at
 // once: 4 waves (126 VGPRs) keep it out of scratch (256^3 projection, 1e9 rays
 // at 0 / 0.785 rad, a ray id per lane: 29.1 / 31.6 ms; 6 waves with 180 B of scratch 36.8 / 50.6,
-// 8 with 244 B 46.2 / 68.3).  The fixed-step chain fits 8.
+// 8 with 244 B 46.2 / 68.3).  So do the fixed-step chain's (107 VGPRs; 8 waves
+// would take 196 B of scratch).
 template <class C>
 struct WavesHint {
     static constexpr int value = 1;
@@ -263,7 +264,7 @@ struct WavesHint<Chain<MXR_SRC_CONE_BEAM, MXR_SLIT, MXR_PHANTOM, MXR_DETECTOR>> 
 };
 template <>
 struct WavesHint<Chain<MXR_SRC_CONE_BEAM, kPhantomStep, MXR_DETECTOR>> {
-    static constexpr int value = 8;
+    static constexpr int value = 4;
 };
 // the scattering chain holds three walks: 6 waves (at most 80 VGPRs)
 // measured 17 % faster than its natural 141 VGPRs at 3 waves, and than 4 or 8
@@ -353,10 +354,14 @@ __device__ __forceinline__ TallyHit run_tallied(Chain<Ts...>, const DevInstr *in
     to_local(ph, ray, q, dl);
     const double *mu_row = mu_lds + mu_row_of(ph, ray.E, n_ebin) * n_mat;
     double tau = 0.0;
+    double inv[3], a_in, a_out;
     if constexpr (T[N - 2] == kPhantomStep) {
-        if (live) tau = step_tau(phantom_geo(ph), q, dl, ph.par[3], (int)ph.aux[5], mu_row);
+        StepPath p{};
+        const bool in = live && step_path(phantom_geo(ph), q, dl, ph.par[3], (int)ph.aux[5], inv, a_in, a_out, p);
+        tau = bundle_tau<true, true>((const MXR_CONSTANT DevComp *)&ph, (const MXR_CONSTANT uint8_t *)ins->bricks, q, dl, inv,
+                                     a_in, a_out, in, mu_row, &p);
+        tau = in ? tau : 0.0;
     } else {
-        double inv[3], a_in, a_out;
         const bool in = live && volume_chord(phantom_geo(ph), q, dl, inv, a_in, a_out);
         tau = bundle_tau<EXACT>((const MXR_CONSTANT DevComp *)&ph, (const MXR_CONSTANT uint8_t *)ins->bricks, q, dl, inv, a_in, a_out, in,
                                 mu_row);
@@ -1599,8 +1604,7 @@ static void plan_tiles(RunArgs &a, const DevInstr &d, const PropTable *prop) {
     TilePlan &tp = a.tp;
     tp = TilePlan{};
     const bool whole = a.first == 0 && a.n == a.n_total;
-    const bool steps = d.phantom >= 0 && (d.c[d.phantom].flags & 1u);
-    while (!steps && tp.rounds < 4 && (a.n >> (8 + 14 + tp.rounds + 1)) > 0) ++tp.rounds;
+    while (tp.rounds < 4 && (a.n >> (8 + 14 + tp.rounds + 1)) > 0) ++tp.rounds;
     auto log2_of = [](double x, uint32_t most) {
         uint32_t l = 0;
         while (l < most && x > 1.4142 * (double)(1u << l)) ++l;
@@ -1637,7 +1641,7 @@ static void plan_tiles(RunArgs &a, const DevInstr &d, const PropTable *prop) {
         }
     } else {
         add(0, a.n, a.G, 1.0);
-        tp.cull = tp.rounds > 0 || steps;
+        tp.cull = tp.rounds > 0;
     }
     // the private histogram: a window of up to 1024 bins, for monitors whose
     // bins fit the tags
