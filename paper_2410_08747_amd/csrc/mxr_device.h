@@ -42,6 +42,8 @@ __device__ __forceinline__ const MXR_CONSTANT T *again(const MXR_CONSTANT T *p) 
 constexpr double kHc = 12.398419843320026;  // keV * Angstrom (CODATA 2018)
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kTwoPi = 2.0 * 3.14159265358979323846;
+// log 2 in two parts: its first 32 bits and the rest
+constexpr double kLog2Hi = 0x1.62e42fee00000p-1, kLog2Lo = 0x1.a39ef35793c76p-33;
 constexpr double kInf = __builtin_huge_val();
 
 enum RayStatus : int32_t { kAlive = 0, kExited = 1, kAbsorbed = 2 };
@@ -174,18 +176,20 @@ struct RunArgs {
 
 // ------------------------------------------------------------- Philox ----
 // Philox4x32-10 (Salmon et al., SC'11).  The 32x32->64 products map to
-// v_mad_u64_u32.
+// v_mad_u64_u32, the two exclusive ors of a word to one v_bitop3_b32.
 struct Philox {
     uint32_t k0, k1, c1, c2, c3;
 
     __device__ __forceinline__ void block(uint32_t j, uint32_t out[4]) const {
         uint32_t x0 = j, x1 = c1, x2 = c2, x3 = c3, a = k0, b = k1;
+        // the round keys are added up (in scalar registers) for each block: kept
+        // for a whole kernel they end up in lanes of a vector register
 #pragma unroll
         for (int r = 0; r < 10; ++r) {
             uint64_t pa = (uint64_t)0xD2511F53u * x0;
             uint64_t pb = (uint64_t)0xCD9E8D57u * x2;
-            uint32_t y0 = (uint32_t)(pb >> 32) ^ x1 ^ a;
-            uint32_t y2 = (uint32_t)(pa >> 32) ^ x3 ^ b;
+            const uint32_t y0 = __builtin_amdgcn_bitop3_b32((uint32_t)(pb >> 32), x1, a, 0x96);
+            const uint32_t y2 = __builtin_amdgcn_bitop3_b32((uint32_t)(pa >> 32), x3, b, 0x96);
             x1 = (uint32_t)pb;
             x3 = (uint32_t)pa;
             x0 = y0;
@@ -197,9 +201,11 @@ struct Philox {
     }
 };
 
+// ((w >> 12) + 1/2) 2^-52 of the 64-bit word w: 1 + (w >> 12) 2^-52 by its bits,
+// less 1 - 2^-53 (exact: the result has 53 bits).
 __device__ __forceinline__ double u01(uint32_t lo, uint32_t hi) {
-    uint64_t w = ((uint64_t)hi << 32) | lo;
-    return ((double)(w >> 12) + 0.5) * 0x1.0p-52;
+    const uint64_t w = ((uint64_t)hi << 32) | lo;
+    return __longlong_as_double((long long)((w >> 12) | 0x3FF0000000000000ull)) - 0x1.fffffffffffffp-1;
 }
 
 // Uniforms of one ray, produced two at a time on demand.
@@ -270,6 +276,124 @@ __device__ __forceinline__ bool plane_z0(double q[3], const double dl[3]) {
     return true;
 }
 
+// ------------------------------------------- functions of known ranges ----
+// The library's sqrt, log, sincos and division take any argument: scaling of
+// subnormals, reductions of huge angles, infinities.  Where the range is known
+// (uniforms, unit vectors, values near 1) the forms below leave that out, at the
+// same accuracy (about an ulp of the exact result).  Instructions for 64 rays of
+// the lens instrument 1609 -> 1220 and of the beamline 2000 -> 1620, both bound
+// by VALU issue: 1e8 rays 4.45 -> 3.26 ms and 5.04 -> 4.20 ms.  (A polynomial
+// asin for the mirror and the crystals gave the beamline less than 1 %.)
+
+// A constant in scalar registers: a 64-bit one costs a polynomial's step two
+// moves into vector registers otherwise (the Gaussian source and crop 18 % of
+// their instructions).
+__device__ __forceinline__ double scalar(double c) {
+    return c;
+}
+
+// 1 / d, d positive or negative and normal with a normal reciprocal: two Newton
+// steps from the hardware's estimate (about 23 bits).
+__device__ __forceinline__ double rcp_normal(double d) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return fma(fma(-d, r, 1.0), r, r);
+}
+// a / d from r = rcp_normal(d), corrected by its remainder: the rounded quotient.
+__device__ __forceinline__ double div_normal(double a, double d, double r) {
+    const double q = a * r;
+    return fma(fma(-d, q, a), r, q);
+}
+// sqrt(x), x normal and positive: one coupled Newton step for the root and
+// half its reciprocal, then the root's remainder.
+__device__ __forceinline__ double sqrt_normal(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = fma(-g, h, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    return fma(fma(-g, g, x), h, g);
+}
+
+// sqrt(x) of a finite x >= 0, and 1 / sqrt(x) of a normal one (a second step for
+// the reciprocal).
+__device__ __forceinline__ double sqrt_finite(double x) {
+    const double r = sqrt_normal(x);
+    return x > 0.0 ? r : 0.0;
+}
+__device__ __forceinline__ double rsqrt_normal(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = fma(-g, h, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    h = fma(h, fma(-g, h, 0.5), h);
+    return h + h;
+}
+
+// log(u), 0 < u < 1 normal: u = 2^k m, m in [sqrt(1/2), sqrt 2), f = m - 1
+// (exact), s = f / (2 + f), log(1 + f) = 2 atanh(s) = f - f^2/2 + s (f^2/2 + R)
+// with the series R = 2 (s^2/3 + s^4/5 + ...) (|s| < 0.172: the first term left
+// out is below 2e-18), added smallest first to k log 2 in two parts (the first
+// of 32 bits, so that its multiples are exact).
+__device__ __forceinline__ double log_unit(double u) {
+    double m = __builtin_amdgcn_frexp_mant(u);
+    int k = __builtin_amdgcn_frexp_exp(u);
+    const bool low = m < 0.70710678118654752;
+    m = low ? m + m : m;
+    k = low ? k - 1 : k;
+    const double f = m - 1.0, s = f * rcp_normal(2.0 + f), z = s * s, half = 0.5 * (f * f), kd = (double)k;
+    double R = 2.0 / 21.0;
+    R = fma(z, R, scalar(2.0 / 19.0));
+    R = fma(z, R, scalar(2.0 / 17.0));
+    R = fma(z, R, scalar(2.0 / 15.0));
+    R = fma(z, R, scalar(2.0 / 13.0));
+    R = fma(z, R, scalar(2.0 / 11.0));
+    R = fma(z, R, scalar(2.0 / 9.0));
+    R = fma(z, R, scalar(2.0 / 7.0));
+    R = fma(z, R, scalar(2.0 / 5.0));
+    R = fma(z, R, scalar(2.0 / 3.0));
+    const double lo = fma(kd, scalar(kLog2Lo), s * fma(z, R, half));
+    return fma(kd, scalar(kLog2Hi), -((half - lo) - f));
+}
+
+// sin y and cos y for |y| <= pi/4 from their Maclaurin series through y^17
+// and y^18 (the first omitted terms, y^19/19! and y^20/20!, are below 1e-19
+// there), evaluated by Horner's rule in fused multiply-adds.
+__device__ __forceinline__ void sincos_quarter(double y, double &sn, double &cs) {
+    const double y2 = y * y;
+    double p = -1.0 / 355687428096000.0;
+    p = fma(y2, p, scalar(1.0 / 1307674368000.0));
+    p = fma(y2, p, scalar(-1.0 / 6227020800.0));
+    p = fma(y2, p, scalar(1.0 / 39916800.0));
+    p = fma(y2, p, scalar(-1.0 / 362880.0));
+    p = fma(y2, p, scalar(1.0 / 5040.0));
+    p = fma(y2, p, scalar(-1.0 / 120.0));
+    p = fma(y2, p, scalar(1.0 / 6.0));
+    sn = fma(-(y * y2), p, y);
+    double q = 1.0 / 6402373705728000.0;
+    q = fma(y2, q, scalar(-1.0 / 20922789888000.0));
+    q = fma(y2, q, scalar(1.0 / 87178291200.0));
+    q = fma(y2, q, scalar(-1.0 / 479001600.0));
+    q = fma(y2, q, scalar(1.0 / 3628800.0));
+    q = fma(y2, q, scalar(-1.0 / 40320.0));
+    q = fma(y2, q, scalar(1.0 / 720.0));
+    q = fma(y2, q, scalar(-1.0 / 24.0));
+    q = fma(y2, q, scalar(0.5));
+    cs = fma(-y2, q, 1.0);
+}
+
+// sin and cos of 2 pi u, 0 <= u < 1: the nearest quarter turn taken off exactly.
+__device__ __forceinline__ void sincos_turn(double u, double &sn, double &cs) {
+    const double k = rint(4.0 * u);
+    double a, b;
+    sincos_quarter(kTwoPi * fma(k, -0.25, u), a, b);
+    const int n = (int)k;
+    const double c0 = n & 1 ? b : a, c1 = n & 1 ? a : b;
+    sn = n & 2 ? -c0 : c0;
+    cs = (n + 1) & 2 ? -c1 : c1;
+}
+
 // ------------------------------------------------------------ sources ----
 // Square emitter, cone uniform in solid angle: with s = sqrt(U) sin(a/2) =
 // sin(theta/2), sin(theta) = 2 s sqrt(1 - s^2) and cos(theta) = 1 - 2 s^2,
@@ -279,10 +403,10 @@ __device__ __forceinline__ void src_rect_cone(const DevComp &c, Stream &s, Ray &
     q[0] = (s.u(0) - 0.5) * c.par[0];
     q[1] = (s.u(1) - 0.5) * c.par[1];
     q[2] = 0.0;
-    double sh = sqrt(s.u(2)) * c.aux[0];
+    double sh = sqrt_normal(s.u(2)) * c.aux[0];
     double ch = sqrt(1.0 - sh * sh);
     double sinp, cosp;
-    sincos(kTwoPi * s.u(3), &sinp, &cosp);
+    sincos_turn(s.u(3), sinp, cosp);
     double st = 2.0 * sh * ch;
     dl[0] = st * cosp;
     dl[1] = st * sinp;
@@ -344,32 +468,6 @@ __device__ __forceinline__ StratCell strat_cell(const StratDiv &s, uint64_t i) {
     return {cx, cy, count == s.c0 ? s.f0 : s.f1};
 }
 
-// sin y and cos y for |y| <= pi/4 from their Maclaurin series through y^17
-// and y^18 (the first omitted terms, y^19/19! and y^20/20!, are below 1e-19
-// there), evaluated by Horner's rule in fused multiply-adds.
-__device__ __forceinline__ void sincos_quarter(double y, double &sn, double &cs) {
-    const double y2 = y * y;
-    double p = -1.0 / 355687428096000.0;
-    p = fma(y2, p, 1.0 / 1307674368000.0);
-    p = fma(y2, p, -1.0 / 6227020800.0);
-    p = fma(y2, p, 1.0 / 39916800.0);
-    p = fma(y2, p, -1.0 / 362880.0);
-    p = fma(y2, p, 1.0 / 5040.0);
-    p = fma(y2, p, -1.0 / 120.0);
-    p = fma(y2, p, 1.0 / 6.0);
-    sn = fma(-(y * y2), p, y);
-    double q = 1.0 / 6402373705728000.0;
-    q = fma(y2, q, -1.0 / 20922789888000.0);
-    q = fma(y2, q, 1.0 / 87178291200.0);
-    q = fma(y2, q, -1.0 / 479001600.0);
-    q = fma(y2, q, 1.0 / 3628800.0);
-    q = fma(y2, q, -1.0 / 40320.0);
-    q = fma(y2, q, 1.0 / 720.0);
-    q = fma(y2, q, -1.0 / 24.0);
-    q = fma(y2, q, 0.5);
-    cs = fma(-y2, q, 1.0);
-}
-
 // Concentric map of (ca, cb) in [-1, 1]^2 onto the unit disk: radius rad
 // and the angle's sine and cosine.  The angle is (pi/4) x with x = cb/ca,
 // or pi/2 - (pi/4) x with x = ca/cb, |x| <= 1; both come from sin and cos
@@ -381,10 +479,10 @@ __device__ __forceinline__ void concentric(double ca, double cb, double &rad, do
         rad = 0.0;
     } else if (fabs(ca) > fabs(cb)) {
         rad = ca;
-        y = (kPi / 4.0) * (cb / ca);
+        y = (kPi / 4.0) * div_normal(cb, ca, rcp_normal(ca));
     } else {
         rad = cb;
-        y = (kPi / 4.0) * (ca / cb);
+        y = (kPi / 4.0) * div_normal(ca, cb, rcp_normal(cb));
         swap = true;
     }
     double sn, cn;
@@ -527,21 +625,22 @@ __device__ __forceinline__ double tan_small(double x) {
 }
 
 __device__ __forceinline__ void src_gaussian(const DevComp &c, Stream &s, Ray &ray) {
-    double r1 = sqrt(-2.0 * log(s.u(0)));
+    double r1 = sqrt_normal(-2.0 * log_unit(s.u(0)));
     double s1, c1, s2, c2;
-    sincos(kTwoPi * s.u(1), &s1, &c1);
-    double r2 = sqrt(-2.0 * log(s.u(2)));
-    sincos(kTwoPi * s.u(3), &s2, &c2);
+    sincos_turn(s.u(1), s1, c1);
+    double r2 = sqrt_normal(-2.0 * log_unit(s.u(2)));
+    sincos_turn(s.u(3), s2, c2);
     double q[3], dl[3];
     q[0] = c.par[0] * (r1 * c1);
     q[1] = c.par[1] * (r1 * s1);
     q[2] = 0.0;
     double tx = tan_small(c.par[2] * (r2 * c2));
     double ty = tan_small(c.par[3] * (r2 * s2));
-    double nrm = sqrt(tx * tx + ty * ty + 1.0);
-    dl[0] = tx / nrm;
-    dl[1] = ty / nrm;
-    dl[2] = 1.0 / nrm;
+    // (at most 1e18, where tan ends: nrm and its reciprocal are normal)
+    const double nrm = sqrt_normal(tx * tx + ty * ty + 1.0), rn = rcp_normal(nrm);
+    dl[0] = div_normal(tx, nrm, rn);
+    dl[1] = div_normal(ty, nrm, rn);
+    dl[2] = div_normal(1.0, nrm, rn);
     ray.E = c.par[4] * ((1.0 - c.par[5]) + 2.0 * c.par[5] * s.u(4));
     ray.w = 1.0;
     to_lab(c, q, dl, ray);
@@ -604,21 +703,22 @@ __device__ __forceinline__ bool lens_surface(double q[3], double dl[3], double z
     const double C = (q[2] - z0) - (double)S * ((q[0] * q[0] + q[1] * q[1]) * inv_2R);
     const double disc = B * B - 4.0 * A * C;
     if (!(disc >= 0.0)) return false;
-    const double qq = -0.5 * (B + copysign(sqrt(disc), B));
+    const double qq = -0.5 * (B + copysign(sqrt_finite(disc), B));
     if (qq == 0.0) return false;
-    const double t = C / qq;
+    const double t = div_normal(C, qq, rcp_normal(qq));
     if (!(t >= 0.0)) return false;
 #pragma unroll
     for (int i = 0; i < 3; ++i) q[i] = q[i] + t * dl[i];
     if (q[0] * q[0] + q[1] * q[1] > ra2) return false;
     const double g0 = (double)(-S) * (q[0] * inv_R), g1 = (double)(-S) * (q[1] * inv_R);
-    const double inv_gn = 1.0 / sqrt(g0 * g0 + g1 * g1 + 1.0);
+    const double inv_gn = rsqrt_normal(g0 * g0 + g1 * g1 + 1.0);
     const double m0 = g0 * inv_gn, m1 = g1 * inv_gn, m2 = inv_gn;
     const double cos_i = dl[0] * m0 + dl[1] * m1 + dl[2] * m2;
     if (!(cos_i > 0.0)) return false;
     const double k = 1.0 - eta * eta * (1.0 - cos_i * cos_i);
     if (!(k >= 0.0)) return false;
-    const double gc = one_m_eta2 / (sqrt(k) + eta * cos_i);
+    const double den = sqrt_finite(k) + eta * cos_i;
+    const double gc = div_normal(one_m_eta2, den, rcp_normal(den));
     dl[0] = eta * dl[0] + gc * m0;
     dl[1] = eta * dl[1] + gc * m1;
     dl[2] = eta * dl[2] + gc * m2;
@@ -2049,7 +2149,7 @@ __device__ __forceinline__ double darwin(double x) {
 }
 
 __device__ __forceinline__ bool bragg(double q[3], double dl[3], const double P[3], const double N[3],
-                                      double two_d, double half_w, double E, double &R) {
+                                      double th_b, double half_w, double &R) {
     double dn = dl[0] * N[0] + dl[1] * N[1] + dl[2] * N[2];
     if (!(dn < 0.0)) return false;
     double rel0 = q[0] - P[0], rel1 = q[1] - P[1], rel2 = q[2] - P[2];
@@ -2058,7 +2158,6 @@ __device__ __forceinline__ bool bragg(double q[3], double dl[3], const double P[
 #pragma unroll
     for (int i = 0; i < 3; ++i) q[i] = q[i] + t * dl[i];
     double th_in = asin(-dn);
-    double th_b = asin(kHc / (two_d * E));
     R = darwin((th_in - th_b) / half_w);
 #pragma unroll
     for (int i = 0; i < 3; ++i) dl[i] = dl[i] - 2.0 * dn * N[i];
@@ -2070,8 +2169,9 @@ __device__ __forceinline__ bool comp_dcm(const DevComp &c, Ray &ray) {
     double q[3], dl[3], R1, R2;
     to_local(c, ray, q, dl);
     const double P1[3] = {0.0, 0.0, 0.0};
-    if (!bragg(q, dl, P1, c.aux + 0, c.aux[9], c.aux[10], ray.E, R1)) return false;
-    if (!bragg(q, dl, c.aux + 6, c.aux + 3, c.aux[9], c.aux[10], ray.E, R2)) return false;
+    const double th_b = asin(kHc / (c.aux[9] * ray.E));  // both crystals' Bragg angle
+    if (!bragg(q, dl, P1, c.aux + 0, th_b, c.aux[10], R1)) return false;
+    if (!bragg(q, dl, c.aux + 6, c.aux + 3, th_b, c.aux[10], R2)) return false;
     ray.w = ray.w * R1;
     ray.w = ray.w * R2;
     to_lab(c, q, dl, ray);
@@ -2091,8 +2191,6 @@ __device__ __forceinline__ bool comp_powder(const DevComp &c, Stream &s, Ray &ra
     double lambda = kHc / ray.E;
     double sarg = lambda / (2.0 * dsp[j]);
     if (!(sarg <= 1.0)) return false;
-    double tth = 2.0 * asin(sarg);
-    double eta = kTwoPi * s.u((int)c.draw0 + 1);
     double e1x = -dl[2], e1z = dl[0];
     double n1 = sqrt(e1x * e1x + 0.0 * 0.0 + e1z * e1z);
     e1x = e1x / n1;
@@ -2101,9 +2199,10 @@ __device__ __forceinline__ bool comp_powder(const DevComp &c, Stream &s, Ray &ra
     double e2x = dl[1] * e1z - dl[2] * e1y;
     double e2y = dl[2] * e1x - dl[0] * e1z;
     double e2z = dl[0] * e1y - dl[1] * e1x;
-    double st, ct, se, ce;
-    sincos(tth, &st, &ct);
-    sincos(eta, &se, &ce);
+    // the cone angle 2 asin(sarg) by its sine and cosine
+    const double st = 2.0 * sarg * sqrt(1.0 - sarg * sarg), ct = 1.0 - 2.0 * (sarg * sarg);
+    double se, ce;
+    sincos_turn(s.u((int)c.draw0 + 1), se, ce);
     double out[3] = {ct * dl[0] + st * (ce * e1x + se * e2x), ct * dl[1] + st * (ce * e1y + se * e2y),
                      ct * dl[2] + st * (ce * e1z + se * e2z)};
     to_lab(c, q, out, ray);
