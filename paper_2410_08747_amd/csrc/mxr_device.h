@@ -1387,12 +1387,30 @@ struct OpenRun {
     double mu, a_start, tau;
 };
 
+// The same, looking for the depth tau_star on the way (see WalkHit).
+struct FindRun : OpenRun {
+    double tau_star;
+    WalkHit hit;
+};
+
 // Close the run at t (clipped to the path's end, and never set back) and open
 // one of material m.
-__device__ __forceinline__ void turn_run(OpenRun &run, double t, double a_out, uint32_t m,
-                                         const double *__restrict__ mu_row) {
+template <class Run>
+__device__ __forceinline__ void turn_run(Run &run, double t, double a_out, uint32_t m, const double *__restrict__ mu_row) {
     const double tc = max_f64(min_f64(t, a_out), run.a_start);
-    run.tau = fma(run.mu, tc - run.a_start, run.tau);
+    const double tau = fma(run.mu, tc - run.a_start, run.tau);
+    if constexpr (sizeof(Run) > sizeof(OpenRun)) {
+        if (run.mu > 0.0 && tc > run.a_start) {  // as close_run
+            if (!run.hit.found && tau >= run.tau_star) {
+                run.hit.found = true;
+                run.hit.s = run.a_start + (run.tau_star - run.tau) / run.mu;
+                run.hit.m = run.m;
+            }
+            run.hit.last_end = tc;
+            run.hit.last_m = run.m;
+        }
+    }
+    run.tau = tau;
     run.a_start = tc;
     run.m = m;
     run.mu = mu_row[m];
@@ -1446,20 +1464,22 @@ __device__ __forceinline__ RoleStep role_at(const Role &r, const RoleAxis &x, do
 // late, further on, in the layer its position gives.  Events past ae are
 // events of the path all the same; the next stretch or change sees them again
 // as runs of no length (turn_run never sets a run back).
-template <bool EXACT, int K>
+template <bool EXACT, int K, class Run>
 __device__ __forceinline__ void stretch_walk(const MXR_CONSTANT DevComp *ph, int axD, const Role &D, const Role &A,
                                              const Role &B, bool back, int layer, bool late, double as, double ae,
-                                             double a_out, OpenRun &run, const double *__restrict__ mu_row) {
+                                             double a_out, Run &run, const double *__restrict__ mu_row) {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)ph->data0, (short)0, (int)ph->n0, 0x00020000);
     const RoleAxis xD = role_axis(ph, axD), xA = role_axis(ph, axD == 0 ? 1 : 0), xB = role_axis(ph, axD == 2 ? 1 : 2);
+    constexpr bool ONE = sizeof(Run) == sizeof(OpenRun);  // as the event walk's alphas (see siddon_walk)
     const double v = ph->par[0], rv = ph->aux[6];
     const RoleStep a = role_at(A, xA, v, rv, as), b = role_at(B, xB, v, rv, as);
     if (late) layer = role_at(D, xD, v, rv, as).idx;
-    const double cD = back ? -xD.c : xD.c, iD = back ? -D.inv : D.inv, nD = -(D.q * D.inv);
+    const double cD = back ? -xD.c : xD.c, iD = back ? -D.inv : D.inv, nD = -(D.q * D.inv), qD = back ? -D.q : D.q;
+    const double qA = A.d > 0.0 ? A.q : -A.q, qB = B.d > 0.0 ? B.q : -B.q;
     int kD = back ? -layer : layer + 1, kA = a.k, kB = b.k;
     double PD = cD + (double)kD * v, PA = a.P, PB = b.P;
-    double aD = plane_alpha<true>(PD, 0.0, iD, nD);
-    double aA = plane_alpha<true>(PA, 0.0, a.iv, a.nq), aB = plane_alpha<true>(PB, 0.0, b.iv, b.nq);
+    double aD = plane_alpha<ONE>(PD, qD, iD, nD);
+    double aA = a.nq == kInf ? kInf : plane_alpha<ONE>(PA, qA, a.iv, a.nq), aB = b.nq == kInf ? kInf : plane_alpha<ONE>(PB, qB, b.iv, b.nq);
     double mAB = min_f64(aA, aB);
     const int oD = back ? -xD.str : xD.str, dA = a.off - oD, dB = b.off - oD;
     uint32_t off = (uint32_t)(layer * xD.str + a.idx * xA.str + b.idx * xB.str);
@@ -1484,7 +1504,7 @@ __device__ __forceinline__ void stretch_walk(const MXR_CONSTANT DevComp *ph, int
                     if (side && AfirstB) {
                         off += (uint32_t)dA;
                         PA = EXACT ? PA + v : a.c + (double)(++kA) * v;
-                        aA = plane_alpha<true>(PA, 0.0, a.iv, a.nq);
+                        aA = plane_alpha<ONE>(PA, qA, a.iv, a.nq);
                         if constexpr (EXACT) PD = PD - v;
                         else kD -= 1;
                     }
@@ -1493,7 +1513,7 @@ __device__ __forceinline__ void stretch_walk(const MXR_CONSTANT DevComp *ph, int
                     if (side && !AfirstB) {
                         off += (uint32_t)dB;
                         PB = EXACT ? PB + v : b.c + (double)(++kB) * v;
-                        aB = plane_alpha<true>(PB, 0.0, b.iv, b.nq);
+                        aB = plane_alpha<ONE>(PB, qB, b.iv, b.nq);
                         if constexpr (EXACT) PD = PD - v;
                         else kD -= 1;
                     }
@@ -1501,7 +1521,7 @@ __device__ __forceinline__ void stretch_walk(const MXR_CONSTANT DevComp *ph, int
                 mAB = min_f64(aA, aB);
             }
             if constexpr (!EXACT) PD = cD + (double)kD * v;
-            aD = plane_alpha<true>(PD, 0.0, iD, nD);
+            aD = plane_alpha<ONE>(PD, qD, iD, nD);
             o[j] = off;
         }
         uint32_t m[K];
@@ -1588,11 +1608,12 @@ __device__ __forceinline__ int footprint_code(__amdgpu_buffer_rsrc_t rs, uint32_
 // inside the occupied box's layers by every path, also one that passes the box.
 // 5e7 rays in steps of a third of a voxel through 256^3: every step of every
 // ray that reaches the monitor 4.5 ms, this 1.3 ms.
-template <bool EXACT, bool STEP = false>
+template <bool EXACT, bool STEP = false, class Run = OpenRun>
 __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, const MXR_CONSTANT uint8_t *bricks,
                                              const double q[3], const double dl[3], const double inv[3], double a_vol,
                                              double a_out, bool in, const double *__restrict__ mu_row,
-                                             const StepPath *sp = nullptr) {
+                                             const StepPath *sp = nullptr, double tau_star = 0.0, WalkHit *hit_out = nullptr) {
+    constexpr bool ONE = sizeof(Run) == sizeof(OpenRun);  // as the event walk's alphas (see siddon_walk)
     const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     // the dominant axis, as in siddon_tau, and its direction
     const double ax = fabs(dl[0]), ay = fabs(dl[1]), az = fabs(dl[2]);
@@ -1600,7 +1621,9 @@ __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, c
     const int own = 2 * ownD + (pick3(ownD, dl[0], dl[1], dl[2]) < 0.0);
     const MXR_CONSTANT DevComp *const p0 = again(comp);
     const uint32_t bg = (uint32_t)p0->aux[14];
-    OpenRun run{bg, mu_row[bg], a_vol, 0.0};
+    Run run;
+    run.m = bg, run.mu = mu_row[bg], run.a_start = a_vol, run.tau = 0.0;
+    if constexpr (!ONE) run.tau_star = tau_star;
     // the path's part inside the occupied box, as in siddon_tau; outside it
     // the run of background stays open
     double a_box = a_vol, z_box = a_out;
@@ -1609,7 +1632,7 @@ __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, c
     for (int i = 0; i < (STEP ? 0 : 3); ++i) {
         const double lo = p0->aux[8 + i], hi = p0->aux[11 + i];
         const double nq = -(q[i] * inv[i]);
-        const double b0 = fma(lo, inv[i], nq), b1 = fma(hi, inv[i], nq);
+        const double b0 = plane_alpha<ONE>(lo, q[i], inv[i], nq), b1 = plane_alpha<ONE>(hi, q[i], inv[i], nq);
         if (dl[i] != 0.0) {
             a_box = max_f64(a_box, min_f64(b0, b1));
             z_box = min_f64(z_box, max_f64(b0, b1));
@@ -1643,7 +1666,7 @@ __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, c
         const int bLo = Lo / kBrick, bHi = (Hi + kBrick - 1) / kBrick, NB = bHi - bLo;
         const int P0 = bLo * kBrick, P1 = bHi * kBrick < xD.n ? bHi * kBrick : xD.n;
         const double nD = -(D.q * D.inv);
-        auto alpha_of = [&](int plane) { return fma(xD.c + (double)plane * v, D.inv, nD); };
+        auto alpha_of = [&](int plane) { return plane_alpha<ONE>(xD.c + (double)plane * v, D.q, D.inv, nD); };
         float m[8];
         {
             const double e0 = alpha_of(P0), e1 = alpha_of(P1);
@@ -1774,7 +1797,7 @@ __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, c
                     }
                     const double a0 = alpha_of(open), as = max_f64(a0, a_box), ae = min_f64(alpha_of(plane), z_box);
                     if (!STEP && part && ae > as)
-                        stretch_walk<EXACT, kStretchRound>(again(comp), iD, D, A, B, back, back ? open - 1 : open, as > a0, as,
+                        stretch_walk<EXACT, kStretchRound, Run>(again(comp), iD, D, A, B, back, back ? open - 1 : open, as > a0, as,
                                                            ae, a_out, run, mu_row);
                     open = -1;
                 }
@@ -1795,6 +1818,11 @@ __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, c
             }
             if (ended) break;
         }
+    }
+    if constexpr (!ONE) {
+        turn_run(run, a_out, a_out, run.m, mu_row);
+        *hit_out = run.hit;
+        return run.tau;
     }
     return fma(run.mu, a_out - run.a_start, run.tau);
 }
@@ -1949,12 +1977,13 @@ __device__ __forceinline__ bool siddon_locate(const PhantomGeo &g, const double 
 // interaction at the rectangle par 5..7 (centre), 8..10 and 11..13 (half
 // axes), lab frame.  T: the three-channel table (1/cm) in global memory.
 // The 2K + 1 walks (optical depth ahead, interaction point, ..., exit) run
-// as passes of one loop: the event walk in locate mode (tau_star infinite for
+// as passes of one loop (BUNDLE: the first two before it, by a full wave's
+// bundle walk): the event walk in locate mode (tau_star infinite for
 // the depth and exit passes) for the coherent chords, the voxel-by-voxel
 // walk for the chords after an isotropic scatter.
-template <bool EXACT>
-__device__ __forceinline__ bool comp_phantom_scatter(const DevComp &c, Stream &s, Ray &ray, const double *mu_lds,
-                                                     uint32_t n_mat, uint32_t n_ebin) {
+template <bool EXACT, bool BUNDLE>
+__device__ __forceinline__ bool comp_phantom_scatter(const DevComp &c, const DevInstr *ins, Stream &s, Ray &ray,
+                                                     const double *mu_lds, uint32_t n_mat, uint32_t n_ebin) {
     double q[3], dl[3];
     to_local(c, ray, q, dl);
     PhantomGeo g;
@@ -1974,7 +2003,31 @@ __device__ __forceinline__ bool comp_phantom_scatter(const DevComp &c, Stream &s
     const bool aimed = (c.flags & 4u) != 0;
     double E = ray.E, w = ray.w, tau_star = kInf, pint = 0.0;
     int e = 0;
-    for (int pass = 0; pass <= 2 * K; ++pass) {
+    WalkHit hit;
+    // the primary chords of a full wave are walked as a bundle, both passes
+    const bool bundle = BUNDLE && __builtin_amdgcn_ballot_w64(true) == ~0ull;
+    if (bundle) {
+        e = (int)fmin(fmax(floor((E - c.par[1]) * c.aux[3]), 0.0), (double)(n_ebin - 1));
+        const double *mu_row = mu_lds + e * n_mat;
+        double inv[3], a_in, a_out;
+        bool in = volume_chord(g, q, dl, inv, a_in, a_out);
+        const MXR_CONSTANT DevComp *const cc = (const MXR_CONSTANT DevComp *)&c;
+        const MXR_CONSTANT uint8_t *const bricks = (const MXR_CONSTANT uint8_t *)ins->bricks;
+        // (one copy of the walk, the first time for a depth that no path has)
+        double tau = 0.0;
+        for (int look = 0; look < 2; ++look) {
+            hit = WalkHit();
+            const double t = bundle_tau<EXACT, false, FindRun>(cc, bricks, q, dl, inv, a_in, a_out, in, mu_row, nullptr,
+                                                               tau_star, &hit);
+            if (look) break;
+            tau = t;
+            in = in && tau > 0.0;
+            pint = -expm1(-tau);
+            tau_star = -log1p(-s.u((int)c.draw0) * pint);
+        }
+        if (!in) return false;
+    }
+    for (int pass = bundle ? 1 : 0; pass <= 2 * K; ++pass) {
         const int k = pass >> 1;
         const bool locate = (pass & 1) != 0;
         if (!locate) {
@@ -1986,11 +2039,13 @@ __device__ __forceinline__ bool comp_phantom_scatter(const DevComp &c, Stream &s
         // across a wave and take the event walk; chords after an isotropic
         // scatter go voxel by voxel
         const bool coherent = k == 0 || (k == K && aimed);
-        WalkHit hit;
         double tau = 0.0;
-        if (coherent) {
+        if (bundle && pass == 1) {
+        } else if (coherent) {
+            hit = WalkHit();
             tau = siddon_tau<EXACT, true>(g, q, dl, mu_lds + e * n_mat, tau_star, &hit);
         } else {
+            hit = WalkHit();
             double sl = 0.0;
             uint32_t ml = 0;
             if (siddon_locate(g, q, dl, mu_lds + e * n_mat, tau_star, sl, ml, tau)) {
