@@ -530,8 +530,10 @@ __device__ __forceinline__ void src_cone_beam(const DevComp &c, Stream &s, Ray &
 // is inverted.  Phi^-1(p) = -sqrt(2) erfcinv(2p).
 __device__ __forceinline__ double trunc_normal(double Pa, double Pb, double Qa, double Qb, double U) {
     const double pl = Pa + U * (Pb - Pa);
-    if (pl <= 0.5) return -1.4142135623730951 * erfcinv(2.0 * pl);
-    return 1.4142135623730951 * erfcinv(2.0 * (Qb + (1.0 - U) * (Qa - Qb)));
+    const bool low = pl <= 0.5;
+    // one inversion for both sides: a wave's energies fall on either
+    const double z = 1.4142135623730951 * erfcinv(2.0 * (low ? pl : Qb + (1.0 - U) * (Qa - Qb)));
+    return low ? -z : z;
 }
 
 // Cone-beam point source drawing y = (u, v, E), u = dx/dz, v = dy/dz, from
@@ -591,8 +593,8 @@ __device__ __forceinline__ bool src_cone_proposal(const DevComp &c, const PropTa
     // instructions per ray; the two forms differ by a few units in the last
     // place)
     const double w2 = 1.0 + r2;
-    const double n = sqrt(w2);
-    const double J = 1.0 / (w2 * n);
+    const double n = sqrt_normal(w2), w3 = w2 * n;
+    const double J = div_normal(1.0, w3, rcp_normal(w3));
     double q = in_cone ? a.pc[0] * (J * P->inv_omega * c.aux[7]) : 0.0;
     if (in_box) {
         for (int k = 0; k < 8; ++k) {
@@ -604,7 +606,8 @@ __device__ __forceinline__ bool src_cone_proposal(const DevComp &c, const PropTa
         }
     }
     const double p_phys = in_cone ? spectrum(c, y[2]) * J * P->inv_omega : 0.0;
-    double dl[3] = {y[0] / n, y[1] / n, 1.0 / n};
+    const double rn = rcp_normal(n);
+    double dl[3] = {div_normal(y[0], n, rn), div_normal(y[1], n, rn), div_normal(1.0, n, rn)};
     ray.E = y[2];
     ray.w = p_phys > 0.0 ? (p_phys / q) * factor : 0.0;
     from_origin(c, dl, ray);
