@@ -28,15 +28,18 @@ if ROOT not in sys.path:
 
 METRIC = "rays/s (ED-CT projection) + time to 1% per-bin error, learned vs plain"
 N_RAYS = 10**9
-# Algorithmic bytes per emitted ray of the projection: one voxel byte per
-# visit (269.6 visits per emitted ray on this phantom and geometry, ~270) and
-# 24 B of histogram update for the 30.2 % of rays that reach the detector.
+# Bytes per emitted ray of a walk that reads every voxel: one byte per visit
+# (269.6 visits per emitted ray on this phantom and geometry, ~270) and 24 B of
+# histogram update for the 30.2 % of rays that reach the detector.  The kernels
+# read far fewer (rays that miss the monitor end before the walk, the others
+# share looks at whole layers): a rate in these units is a rate of equivalent
+# work, not of traffic.
 BYTES_PER_RAY = 270 * 1 + 0.302 * 24
 HBM_PEAK_GBS = 8000.0
 # wave64 VALU instructions per second: 256 CUs x 4 SIMDs x 2.4 GHz / 4 cycles
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
-# FP64 operations per emitted ray of the projection's walk: ~6 per voxel visit
-# (the plane alpha, two comparisons, the segment length, the optical-depth
+# FP64 operations per emitted ray of the same voxel-by-voxel walk: ~6 per voxel
+# visit (the plane alpha, two comparisons, the segment length, the optical-depth
 # fused multiply-add) over 270 visits, plus ~400 for source, clip and tally
 FP64_FLOP_PER_RAY = 6 * 270 + 400
 # rays of the oracle's timed sample (several seconds of host work each; the per-ray
@@ -337,8 +340,10 @@ def batch_bench(args):
         "data": "synthetic",
         "config": {"workload": "batched_edct", "jobs": len(jobs), "angles": n_ang, "phantoms": sizes,
                    "rays_per_job": args.batch_rays, "strata": STRATA, "parallelism": "none (1 GPU)"},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": None},
+        # bound by VALU issue (not counted per pass); the byte rate is that of a walk
+        # that reads every voxel, which these kernels do not
+        "roofline": {"bound": "valu_issue", "achieved": None, "peak": VALU_ISSUE_PEAK, "unit": "wave64 instructions/s",
+                     "frac": None, "traffic": None, "voxel_walk_equivalent_GBs": achieved},
         "schedule": {"form": ["grid", "persistent", "launches"][sched[0]], "groups_per_cu": sched[1],
                      "tile_rays": sched[2], "branches": sched[3], "autotune_s": t_tune},
         "separate_launches": {"value": n_rays / wall_s, "unit": "rays/s", "ms_per_step": wall_s * 1e3},
@@ -690,8 +695,10 @@ def stepping_bench(args):
         "config": {"workload": "edct_projection_fixed_step", "n_rays": n, "step_mm": args.step,
                    "phantom": "256^3 uint8, 1 mm voxels, seed 1", "detector": "256x64 px x 128 E-bins",
                    "strata": STRATA, "parallelism": "none (1 GPU)"},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(PROFILE_STEP)},
+        # bound by VALU issue (its counts: the committed profile); the byte rate
+        # is that of a walk that reads every step's voxel
+        "roofline": {"bound": "valu_issue", "achieved": None, "peak": VALU_ISSUE_PEAK, "unit": "wave64 instructions/s",
+                     "frac": None, "traffic": measured_traffic(PROFILE_STEP), "voxel_walk_equivalent_GBs": achieved},
         "steps_per_ray": steps,
         "exact": {"kernel_ms": e["ms"], "rays_per_s": n / (e["ms"] * 1e-3), "visits_per_ray": visits_per_ray(exact)},
         "time_vs_exact": s["ms"] / e["ms"],
@@ -1119,8 +1126,12 @@ def main():
         "data": "synthetic",
         "config": {"workload": "edct_projection", "n_rays": n, "phantom": "256^3 uint8, 1 mm voxels, seed 1",
                    "detector": "256x64 px x 128 E-bins", "strata": STRATA, "parallelism": "none (1 GPU)"},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": traffic},
+        # VALU instruction issue binds: the launch's committed SQ_INSTS_VALU
+        # count over this run's kernel time, against one wave64 instruction per
+        # SIMD per 4 cycles (null when the kernel sources changed since)
+        "roofline": {"bound": "valu_issue", "achieved": None if valu is None else valu / (kern_ms * 1e-3),
+                     "peak": VALU_ISSUE_PEAK, "unit": "wave64 instructions/s",
+                     "frac": None if valu is None else valu / (kern_ms * 1e-3) / VALU_ISSUE_PEAK, "traffic": traffic},
         "kernel_ms": kern_ms,
         "kernel_ms_median": kern_ms_median,
         "end_to_end": {"median_ms": e2e * 1e3, "repeats": 5, "rays_per_s": n / e2e,
@@ -1128,23 +1139,18 @@ def main():
                                    "phantom scan) + the run + the 3 x 16 MiB image copied to the host"},
         "detected_fraction": detected / n,
         # the same time against the other limits: the HBM bytes the counters
-        # measured (the volume stays in the caches) and the FP64 arithmetic
-        # of the walk (about 6 operations per voxel visit + 400 per ray of
-        # source, clip and tally: a model count of 2.0 kflop per ray)
+        # measured, the FP64 operations they counted, and what a walk that reads
+        # every voxel would move and compute in it
         "roofline_detail": {
-            "gather_model": "1 B per voxel visit (270 per ray) + 24 B per detected ray; L2/MALL-resident, "
-                            "the HBM proxy this workload is quoted on",
+            "voxel_walk_equivalent": {"bytes_per_ray": BYTES_PER_RAY, "GBs": achieved,
+                                      "flop_per_ray": FP64_FLOP_PER_RAY,
+                                      "TFLOPs": FP64_FLOP_PER_RAY * n / (kern_ms * 1e-3) / 1e12},
             "measured_hbm": (None if traffic is None else
                              {"bytes_per_launch": traffic, "achieved_GBs": traffic / (kern_ms * 1e-3) / 1e9,
                               "frac": traffic / (kern_ms * 1e-3) / 1e9 / HBM_PEAK_GBS}),
-            "fp64": {"flop_per_ray": FP64_FLOP_PER_RAY, "achieved_TFLOPs": FP64_FLOP_PER_RAY * n / (kern_ms * 1e-3) / 1e12,
-                     "peak_TFLOPs": 78.6, "frac": FP64_FLOP_PER_RAY * n / (kern_ms * 1e-3) / 78.6e12,
-                     # the same from the committed FP64 op-class counters
-                     "measured_flop_per_ray": (None if fp64 is None else fp64 / n),
+            # from the committed FP64 op-class counters
+            "fp64": {"peak_TFLOPs": 78.6, "measured_flop_per_ray": (None if fp64 is None else fp64 / n),
                      "measured_frac": (None if fp64 is None else fp64 / (kern_ms * 1e-3) / 78.6e12)},
-            # the binding limit: VALU instruction issue (the launch's committed
-            # SQ_INSTS_VALU count over this run's kernel time, against one
-            # wave64 VALU instruction per SIMD per 4 cycles)
             "valu_issue": (None if valu is None else
                            {"insts_per_launch": valu, "achieved_per_s": valu / (kern_ms * 1e-3),
                             "peak_per_s": VALU_ISSUE_PEAK, "frac": valu / (kern_ms * 1e-3) / VALU_ISSUE_PEAK}),
