@@ -240,7 +240,8 @@ void mxr_instrument_destroy(mxr_instrument *ins);
  *   occupancy  waves per SIMD the run kernel is compiled for: 0 the chain's
  *              own, or 4, 6, 8 (fixed chains only; others ignore it)
  *   compact    1: chains with a crop right after the source run the
- *              survivor-compacting kernel; 0: one ray per lane
+ *              survivor-compacting kernel (but for runs too small to fill
+ *              its rounds); 0: one ray per lane
  *   rounds     compacting kernel: 64-ray rounds per wave, 1..64 (0 = 64)
  *   xcd_order  which ray tiles (256 rays; projections up to 4096) each of the eight XCDs traces: 0, the
  *              i-th XCD the i-th eighth of the ray range; 1, launch order;

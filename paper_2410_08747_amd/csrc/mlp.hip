@@ -30,7 +30,7 @@ constexpr int kIn = MXR_MLP_IN, kHid = MXR_MLP_HIDDEN, kOut = MXR_MLP_OUT;
 constexpr uint64_t kW1 = 0, kB1 = kW1 + kIn * kHid, kW2 = kB1 + kHid, kB2 = kW2 + kHid * kHid;
 constexpr uint64_t kW3 = kB2 + kHid, kB3 = kW3 + kHid * kOut, kParams = kB3 + kOut;
 static_assert(kParams == MXR_MLP_PARAMS, "parameter layout");
-constexpr uint64_t kSplitRows = 1024;  // rows per split of a weight-gradient product
+constexpr uint64_t kSplitRows = 1024;  // rows per partial gradient that the workspace has room for
 constexpr int kThreads = 256;
 
 typedef short v4s __attribute__((ext_vector_type(4)));
@@ -288,7 +288,8 @@ struct StripArgs {
     float *out;         // kForward, kForwardOnly
     float *part;        // gridDim.x x kParams partial gradients
     double *loss_part;  // gridDim.x partial losses
-    // layer values (kForward, kGradient)
+    // layer values (kForward, kGradient), stored up to 16 bytes at a time, which
+    // in global memory needs the alignment of a float only
     uint16_t *X, *H1, *H2, *wt;
     float *Z1, *Z2, *O;
     // kGradient

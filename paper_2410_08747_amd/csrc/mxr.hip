@@ -1711,7 +1711,13 @@ static mxr_status launch(mxr_instrument *ins, const RunArgs &base, uint64_t n, b
     if (ledger) shmem += (size_t)(4 * ins->host.ncomp + 1) * sizeof(double);
     if (kc) {
         int32_t off[MXR_MAX_DETECTORS];
-        shmem = lds_tally_layout(ins->host, off);
+        const size_t lds = lds_tally_layout(ins->host, off);
+        // below 8 rounds a wave the queue hardly fills a wave before its flush:
+        // without a private monitor to gain from, one ray per lane is faster
+        // (basic instrument, 1e5 / 3e5 / 1e6 rays: 9.4 / 14.7 / 34.8 us
+        // compacting, 8.5 / 12.9 / 33.1 not; 3e6 rays: 90.4 and 93.3)
+        if (lds == 0 && n < (uint64_t)kBlock * 4 * 8 * ins->n_cu) kc = nullptr;
+        else shmem = lds;
     }
     // one lane per ray; a launch's grid is counted in work-items with 32 bits,
     // so a launch takes at most kMaxLaunchGroups work-groups and longer ray
