@@ -1681,6 +1681,18 @@ static hipError_t launch_tiles(KernelFn k, const DevInstr *dev, RunArgs a, size_
     return hipSuccess;
 }
 
+// Whether a proposal run takes the event walk, one ray a lane at 8 waves per
+// SIMD, rather than the image kernel: its rays nearly all reach the monitor, so
+// the bundle's 4 waves have to pay by the walk alone.  They do not below 2^19
+// rays (one round of the chip; 16 replicas of 3.6e5 rays, 93^3: 885 us so, 1088
+// by tiles), nor in small phantoms before the tiles are large enough for a
+// private histogram (2e6 rays, 47^3 / 93^3: 2388 / 3088 us, tiles 2735 / 3862;
+// 171^3 / 240^3: 4805 / 7253 and 4436 / 4612).
+static bool small_proposal(const DevInstr &d, uint64_t n) {
+    const uint32_t *dims = d.c[1].dims;
+    return n < (1ull << 19) || (n < (1ull << 23) && std::max({dims[0], dims[1], dims[2]}) < 128);
+}
+
 static mxr_status launch(mxr_instrument *ins, const RunArgs &base, uint64_t n, bool ledger, bool trace,
                          hipStream_t stream) {
     const bool exact = ins->host.phantom < 0 || ins->host.c[ins->host.phantom].aux[4] != 0.0;
@@ -1698,7 +1710,11 @@ static mxr_status launch(mxr_instrument *ins, const RunArgs &base, uint64_t n, b
     if (plain && ins->recipe == kRecipeEdctScatter && ins->host.c[1].par[4] == 1.0 &&
         (ins->shape.occupancy == 0 || ins->shape.occupancy == 4))
         k = exact ? k_trace<ChainEdctScatterOnce, false, false, true> : k_trace<ChainEdctScatterOnce, false, false, false>;
-    if (is_image_kernel(ins->recipe, ledger, trace, exact, mode)) {
+    const bool small = mode == kModeProposal && ins->recipe == kRecipeEdct && !ledger && !trace &&
+                       small_proposal(ins->host, n);
+    if (small)
+        k = exact ? k_trace<ChainEdctProposal, false, false, true, 8> : k_trace<ChainEdctProposal, false, false, false, 8>;
+    if (!small && is_image_kernel(ins->recipe, ledger, trace, exact, mode)) {
         RunArgs a = base;
         a.xcd_order = plain ? ins->shape.xcd_order : ins->order;
         plan_tiles(a, ins->host, base.prop ? &ins->prop_host : nullptr);
