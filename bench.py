@@ -91,8 +91,8 @@ def parse():
     return p.parse_args()
 
 
-KERNEL_SOURCES = ["paper_2410_08747_amd/csrc/mxr.hip", "paper_2410_08747_amd/csrc/mxr_device.h", "include/mxr.h",
-                  "paper_2410_08747_amd/build.py"]
+KERNEL_SOURCES = ["paper_2410_08747_amd/csrc/mxr.hip", "paper_2410_08747_amd/csrc/mxr_device.h",
+                  "paper_2410_08747_amd/csrc/mxr_tiles.h", "include/mxr.h", "paper_2410_08747_amd/build.py"]
 PROFILE = "profiles/k_trace_edct_projection_256.md"
 PROFILE_STEP = "profiles/k_trace_edct_step_256.md"
 PROFILE_CRL = "profiles/k_trace_crl_focusing.md"

@@ -534,12 +534,6 @@ __device__ __forceinline__ LdsTally lds_tally(double *smem, uint32_t slots) {
     return t;
 }
 
-// First ray id of a row.
-__device__ __forceinline__ uint64_t row_start(const TileRange &r, uint32_t row) {
-    const uint64_t x = (uint64_t)row * r.rem + r.rows - 1;
-    return r.first + (uint64_t)row * r.q + div_est(x, r.rows, r.r_rows, r.rows);
-}
-
 template <class C, bool EXACT, int WAVES = WavesHint<C>::value>
 __global__ __launch_bounds__(kBlock, WAVES) void k_image(const MXR_CONSTANT_PARAM DevInstr *__restrict__ insc,
                                                          RunArgs a) {
@@ -553,20 +547,17 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_image(const MXR_CONSTANT_PARA
         ++ri;
     }
     const TileRange &r = a.tp.r[ri];
-    const uint32_t per_row = (256u << a.tp.rounds) >> r.ht;  // ids of a tile's row
-    const uint64_t block = div_est(tile, r.cols, r.r_cols, r.rows);
-    const uint64_t col0 = (tile - block * r.cols) * per_row;
-    const uint32_t row0 = (uint32_t)(block << r.ht);
+    const TileAt at = tile_at(r, a.tp.rounds, tile);
     const DevComp &det = ins->c[ins->ncomp - 1];
     if (a.tp.cull) {
         // the tile's cells: rows of cells are rows of ids, and the id at
         // place o of a row lies in cell floor(o G^2 / n + x), 0 <= x < G^2 / n
         const double per = (double)a.sd.G2 * a.sd.rn, G = (double)a.sd.G;
-        const double last = (double)(col0 + per_row < r.q + 1 ? col0 + per_row - 1 : r.q);
-        const double u0 = 2.0 * (floor((double)col0 * per - 1e-6) / G) - 1.0;
+        const double last = (double)(at.col0 + at.per_row < r.q + 1 ? at.col0 + at.per_row - 1 : r.q);
+        const double u0 = 2.0 * (floor((double)at.col0 * per - 1e-6) / G) - 1.0;
         const double u1 = 2.0 * ((floor((last + 1.0) * per + 1e-6) + 1.0) / G) - 1.0;
-        const uint32_t row1 = row0 + (1u << r.ht) < r.rows ? row0 + (1u << r.ht) : r.rows;
-        const double v0 = 2.0 * ((double)row0 / G) - 1.0, v1 = 2.0 * ((double)row1 / G) - 1.0;
+        const uint32_t row1 = at.row0 + (1u << r.ht) < r.rows ? at.row0 + (1u << r.ht) : r.rows;
+        const double v0 = 2.0 * ((double)at.row0 / G) - 1.0, v1 = 2.0 * ((double)row1 / G) - 1.0;
         if (bundle_misses(ins->c[0], det, 0.5 * (u0 + u1), 0.5 * (v0 + v1), 0.5 * (u1 - u0) + 1e-9, 0.5 * (v1 - v0) + 1e-9))
             return;  // whole work-group
     }
@@ -586,8 +577,6 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_image(const MXR_CONSTANT_PARA
     }
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t wide = 64u >> r.hw;                // ids of a wave's row
-    const uint32_t across = per_row / wide;           // waves side by side in a tile
     const uint32_t turns = 4u << a.tp.rounds;         // a wave's worth of rays, of the tile
     const MXR_CONSTANT RunArgs *args =
         (const MXR_CONSTANT RunArgs *)((const MXR_CONSTANT char *)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(void *));
@@ -596,13 +585,8 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_image(const MXR_CONSTANT_PARA
         const DevInstr *ins = (const DevInstr *)again((const MXR_CONSTANT DevInstr *)insc);
         const RunArgs &a = *(const RunArgs *)again(args);
         const TileRange &r = a.tp.r[ri];
-        const uint32_t row = row0 + ((t / across) << r.hw) + lane / wide;
-        const uint64_t col = col0 + (t % across) * wide + lane % wide;
-        const bool in = row < r.rows;
-        const uint64_t at = row_start(r, in ? row : 0);
-        const uint64_t len = in ? row_start(r, row + 1) - at : 0;
-        const bool live = col < len;
-        const uint64_t ray_id = live ? at + col : r.first;  // a lane without a ray holds the range's first, dead
+        uint64_t ray_id;
+        const bool live = tile_ray(r, at, t, lane, ray_id);
         const TallyHit hit = run_tallied<EXACT, kWalkRound>(C{}, ins, ray_id, live, a, mu_lds, n_mat, n_ebin);
         if (!hit.live) continue;
         bool done = false;
@@ -1603,44 +1587,18 @@ void mxr_instrument_destroy(mxr_instrument *ins) {
     delete ins;
 }
 
-// Tiles of a launch of an image kernel over rays [a.first, a.first + a.n).
-// Rounds per tile: as many (at most 16) as leave 16,384 tiles, some 16 to a
-// work-group's place on the chip (of a plain cone's tiles 70 % end at once).
-// A whole run's tiles follow the rows of its stratified ranges; a part of a run
-// is one row.  Rows per tile and per wave make both about square on the
-// monitor: a cell holds c rays, so a wave covers 64 / c cells, `ratio` times
-// as wide as high in a proposal's components.
+// Tiles of a launch of an image kernel over rays [a.first, a.first + a.n).  A
+// whole run's tiles follow the rows of its stratified ranges; a part of a run
+// is one row.
 static void plan_tiles(RunArgs &a, const DevInstr &d, const PropTable *prop) {
     TilePlan &tp = a.tp;
     tp = TilePlan{};
     const bool whole = a.first == 0 && a.n == a.n_total;
-    while (tp.rounds < 4 && (a.n >> (8 + 14 + tp.rounds + 1)) > 0) ++tp.rounds;
-    auto log2_of = [](double x, uint32_t most) {
-        uint32_t l = 0;
-        while (l < most && x > 1.4142 * (double)(1u << l)) ++l;
-        return l;
-    };
+    tp.rounds = tile_rounds(a.n);
     auto add = [&](uint64_t first, uint64_t n, uint64_t rows, double ratio) {
         if (n == 0) return;
-        TileRange &r = tp.r[tp.ranges++];
-        r.first = first;
-        r.n = n;
-        r.rows = (uint32_t)rows;
-        r.q = n / rows;
-        r.rem = (uint32_t)(n % rows);
-        r.r_rows = 1.0 / (double)rows;
-        const double c = (double)n / ((double)rows * (double)rows);
-        uint32_t most = 0;  // at most all rows, and at least 8 ids of a row per wave
-        while (most < 3 && (2ull << most) <= rows) ++most;
-        r.hw = rows > 1 ? log2_of(std::sqrt(64.0 / c * ratio), most) : 0;
-        most = r.hw;
-        while (most < r.hw + 2 + tp.rounds && (2ull << most) <= rows) ++most;
-        r.ht = rows > 1 ? std::max(r.hw, log2_of(std::sqrt((double)(256u << tp.rounds) / c * ratio), most)) : 0;
-        const uint64_t per_row = (256u << tp.rounds) >> r.ht, len = r.q + (r.rem ? 1 : 0);
-        r.cols = (uint32_t)((len + per_row - 1) / per_row);
-        r.r_cols = 1.0 / (double)r.cols;
-        r.tiles = (uint64_t)r.cols * ((rows + (1ull << r.ht) - 1) >> r.ht);
-        tp.tiles += r.tiles;
+        tp.r[tp.ranges] = tile_range(first, n, rows, ratio, tp.rounds);
+        tp.tiles += tp.r[tp.ranges++].tiles;
     };
     if (!whole) {
         add(a.first, a.n, 1, 1.0);

@@ -18,6 +18,7 @@
 #include <stdint.h>
 
 #include "mxr.h"
+#include "mxr_tiles.h"
 
 namespace mxr {
 
@@ -123,19 +124,6 @@ struct StratDiv {
     uint64_t n, G2, c0, r;
     uint32_t G, pad;
     double rn, rG, rG2, f0, f1;
-};
-
-// Rays [first, first + n) of a tiled launch, laid out in `rows` rows of
-// consecutive ids: row r begins at first + ceil(r n / rows).  The rows of a
-// stratified range are its rows of cells, so the rays at one place of
-// neighbouring rows leave in neighbouring directions.  A tile is 2^ht rows of
-// (tile rays >> ht) ids each; the tiles run along the rows first, `cols` to a
-// block of rows.  A wave takes 2^hw rows of 64 >> hw ids at a time.
-struct TileRange {
-    uint64_t first, n, q, tiles;  // q = n / rows; tiles of this range
-    uint32_t rows, rem;           // rem = n mod rows
-    uint32_t cols, ht, hw, pad;
-    double r_rows, r_cols;        // 1 / rows, 1 / cols, rounded
 };
 
 // The tiles of a launch of the image kernels: 256 << rounds rays each, the
@@ -428,18 +416,7 @@ __device__ __forceinline__ double spectrum(const DevComp &c, double E) {
     return c.aux[6] * ((c.par[3] - E) / E) + c.par[6] * g1 + c.par[8] * g2;
 }
 
-// floor(x / d) from the rounded estimate x * rd (rd = 1/d rounded), for a
-// quotient below 2^32 and at most q_max with q_max d < 2^64: the estimate's
-// relative error is a few 2^-53, so it lies within 1 of the quotient, and
-// one product decides a step down or up.
-__device__ __forceinline__ uint64_t div_est(uint64_t x, uint64_t d, double rd, uint64_t q_max) {
-    uint64_t q = (uint64_t)((double)x * rd);
-    q = q > q_max ? q_max : q;
-    const uint64_t p = q * d;
-    if (p > x) q -= 1;
-    else if (x - p >= d) q += 1;
-    return q;
-}
+// The same as div_est for 32 bits.
 __device__ __forceinline__ uint32_t div_est32(uint32_t x, uint32_t d, double rd, uint32_t q_max) {
     uint32_t q = (uint32_t)((double)x * rd);
     q = q > q_max ? q_max : q;
