@@ -1373,12 +1373,20 @@ struct FindRun : OpenRun {
     WalkHit hit;
 };
 
+// tau plus the depth of a run of length len >= 0.  A run of no length adds
+// nothing, also in an opaque material (mu infinite): a path turns through the
+// materials it meets behind the place where its run closed, or behind its end.
+__device__ __forceinline__ double add_run(double mu, double len, double tau) {
+    const int hi = len > 0.0 ? __double2hiint(mu) : 0;  // the low word alone is a finite number
+    return fma(__hiloint2double(hi, __double2loint(mu)), len, tau);
+}
+
 // Close the run at t (clipped to the path's end, and never set back) and open
 // one of material m.
 template <class Run>
 __device__ __forceinline__ void turn_run(Run &run, double t, double a_out, uint32_t m, const double *__restrict__ mu_row) {
     const double tc = max_f64(min_f64(t, a_out), run.a_start);
-    const double tau = fma(run.mu, tc - run.a_start, run.tau);
+    const double tau = add_run(run.mu, tc - run.a_start, run.tau);
     if constexpr (sizeof(Run) > sizeof(OpenRun)) {
         if (run.mu > 0.0 && tc > run.a_start) {  // as close_run
             if (!run.hit.found && tau >= run.tau_star) {
@@ -1804,7 +1812,7 @@ __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, c
         *hit_out = run.hit;
         return run.tau;
     }
-    return fma(run.mu, a_out - run.a_start, run.tau);
+    return add_run(run.mu, a_out - run.a_start, run.tau);
 }
 
 // ------------------------------------------------- scattering phantom ----
