@@ -1655,9 +1655,23 @@ __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, c
         const int P0 = bLo * kBrick, P1 = bHi * kBrick < xD.n ? bHi * kBrick : xD.n;
         const double nD = -(D.q * D.inv);
         auto alpha_of = [&](int plane) { return plane_alpha<ONE>(xD.c + (double)plane * v, D.q, D.inv, nD); };
+        // the bundle's span is bounded between two planes: those of the box's
+        // layers; with fixed steps, by which a path's last sample lies up to its
+        // reach behind the volume, the planes it enters by and the exit moved on
+        // by that much (spans at two planes bound those between, not beyond)
+        const int end = back ? 0 : xD.n;  // the plane by which paths leave the volume
+        float F0 = (float)P0, F1 = (float)P1;
+        double e0 = alpha_of(back && STEP ? P1 : P0), e1 = alpha_of(back && STEP ? P0 : P1);
+        if constexpr (STEP) {
+            if (back) F0 = (float)P1, F1 = (float)P0;
+            if ((back ? P0 : P1) == end) {
+                const double reach = p0->par[3] * rv * 1.001, beyond = back ? -reach : (double)end + reach;
+                F1 = (float)beyond;
+                e1 = plane_alpha<ONE>(xD.c + beyond * v, D.q, D.inv, nD);
+            }
+        }
         float m[8];
         {
-            const double e0 = alpha_of(P0), e1 = alpha_of(P1);
             const double cA = pick3(iA, ph->aux[0], ph->aux[1], ph->aux[2]), cB = pick3(iB, ph->aux[0], ph->aux[1], ph->aux[2]);
             const float xA0 = (float)(((A.q - cA) + e0 * A.d) * rv), xA1 = (float)(((A.q - cA) + e1 * A.d) * rv);
             const float xB0 = (float)(((B.q - cB) + e0 * B.d) * rv), xB1 = (float)(((B.q - cB) + e1 * B.d) * rv);
@@ -1666,7 +1680,7 @@ __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, c
             m[4] = part ? -xA0 : big, m[5] = part ? -xA1 : big, m[6] = part ? -xB0 : big, m[7] = part ? -xB1 : big;
         }
         wave_min8(m);
-        const float perL = __builtin_amdgcn_rcpf((float)(P1 - P0));
+        const float perL = __builtin_amdgcn_rcpf(F1 - F0);
         const float A0 = m[0], A1 = (m[1] - A0) * perL, B0 = m[2], B1 = (m[3] - B0) * perL;
         const float mA0 = m[4], mA1 = (m[5] - mA0) * perL, mB0 = m[6], mB1 = (m[7] - mB0) * perL;
         // a bundle that stays wide, one in few layers, or one in a volume too
@@ -1674,16 +1688,13 @@ __device__ __forceinline__ double bundle_tau(const MXR_CONSTANT DevComp *comp, c
         const bool narrow = Hi - Lo >= kBundleLayers && (int)ph->dims[0] <= kBundleDim && (int)ph->dims[1] <= kBundleDim &&
                             (int)ph->dims[2] <= kBundleDim && fminf(-m[4] - m[0], -m[5] - m[1]) < kBundleNarrow &&
                             fminf(-m[6] - m[2], -m[7] - m[3]) < kBundleNarrow;
-        // the plane by which paths leave the volume, and a step's reach
-        const int end = back ? 0 : xD.n;
-        const float reach = STEP ? (float)(p0->par[3] * rv) * 1.001f : 0.0f;
         // voxels [a0, a1] x [b0, b1] that the bundle covers between two planes
         int a0, a1, b0, b1;
         auto footprint = [&](int pa, int pb, int nA, int nB) {
-            float fa = (float)(pa - P0), fb = (float)(pb - P0);
+            float fa = (float)pa - F0, fb = (float)pb - F0;
             if constexpr (STEP) {
-                if (back) fa = pa == end ? fa - reach : fa;
-                else fb = pb == end ? fb + reach : fb;
+                if (back) fa = pa == end ? F1 - F0 : fa;
+                else fb = pb == end ? F1 - F0 : fb;
             }
             a0 = clamp0_i32(floor_i32(min_f32(fmaf(fa, A1, A0), fmaf(fb, A1, A0)) - kBundleSlack), nA - 1);
             a1 = clamp0_i32(floor_i32(kBundleSlack - min_f32(fmaf(fa, mA1, mA0), fmaf(fb, mA1, mA0))), nA - 1);
