@@ -238,13 +238,17 @@ void mxr_instrument_destroy(mxr_instrument *ins);
  * additions): the rays are independent (paper, section 2.2), so their
  * mapping onto threads is free.
  *   occupancy  waves per SIMD the run kernel is compiled for: 0 the chain's
- *              own, or 4, 6, 8 (fixed chains only; others ignore it)
+ *              own, or 4, 6, 8 (fixed chains only; others ignore it).
+ *              Projections (and photons scattered once) have two forms: 4, the
+ *              rays of a wave cross the phantom as a bundle, in tiles of
+ *              neighbouring source cells; 6 and 8, each ray by itself; 0, the
+ *              library's choice by the run's size and the phantom
  *   compact    1: chains with a crop right after the source run the
  *              survivor-compacting kernel (but for runs too small to fill
  *              its rounds); 0: one ray per lane
  *   rounds     compacting kernel: 64-ray rounds per wave, 1..64 (0 = 64)
- *   xcd_order  which ray tiles (256 rays; projections up to 4096) each of the eight XCDs traces: 0, the
- *              i-th XCD the i-th eighth of the ray range; 1, launch order;
+ *   xcd_order  which ray tiles (256 rays; in bundles up to 4096) each of
+ *              the eight XCDs traces: 0, the i-th XCD the i-th eighth of the ray range; 1, launch order;
  *              2, runs of 64 consecutive tiles dealt to the XCDs in turn.
  *              The default is 1 for instruments with a phantom (the
  *              stratified source sends each block of ray ids through one

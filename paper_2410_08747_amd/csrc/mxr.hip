@@ -239,12 +239,11 @@ __device__ __forceinline__ bool apply_dynamic(const DevComp &c, int k, Ray &ray,
 template <int... Ts>
 struct Chain {};
 
-// Occupancy hint per chain (waves per SIMD the compiler must fit).  The chains
-// that walk an exact phantom as a bundle hold the scan's and a walk's state at
-// once: 4 waves (126 VGPRs) keep it out of scratch (256^3 projection, 1e9 rays
-// at 0 / 0.785 rad, a ray id per lane: 29.1 / 31.6 ms; 6 waves with 180 B of scratch 36.8 / 50.6,
-// 8 with 244 B 46.2 / 68.3).  So do the fixed-step chain's (107 VGPRs; 8 waves
-// would take 196 B of scratch).
+// Occupancy hint per chain (waves per SIMD the compiler must fit).  The kernels
+// that walk a phantom as a bundle hold the scan's and a walk's state at once: 4
+// waves (105 to 128 VGPRs, at most 32 B of scratch) were the fastest (256^3
+// projection, 1e9 rays at 0 / 0.785 rad, a ray id per lane: 29.1 / 31.6 ms; 6
+// waves with 180 B of scratch 36.8 / 50.6, 8 with 244 B 46.2 / 68.3).
 template <class C>
 struct WavesHint {
     static constexpr int value = 1;
@@ -282,6 +281,26 @@ struct WavesHint<Chain<MXR_SRC_CONE_BEAM, kPhantomScatterOnce, MXR_DETECTOR>> {
     static constexpr int value = 4;
 };
 
+// Occupancy of the plain run kernels that end in an absorbing phantom where each
+// ray walks by itself (see walks_as_bundle): 7 waves leave the exact walk the
+// registers for 5 crossings a round, the others fit in 8.
+template <class C>
+struct RayWaves {
+    static constexpr int value = 7;
+};
+template <>
+struct RayWaves<Chain<MXR_SRC_CONE_BEAM, kPhantomStep, MXR_DETECTOR>> {
+    static constexpr int value = 8;
+};
+template <>
+struct RayWaves<Chain<kSrcConeProposal, MXR_PHANTOM, MXR_DETECTOR>> {
+    static constexpr int value = 8;
+};
+template <>
+struct RayWaves<Chain<MXR_SRC_CONE_BEAM, MXR_PHANTOM, kDetectorCollect>> {
+    static constexpr int value = 6;  // 7 spills
+};
+
 // The batch kernels read their per-job arguments from memory rather than the
 // kernel-argument segment; the projection chain takes 4 waves there as well.
 template <class C>
@@ -316,9 +335,9 @@ __device__ __forceinline__ bool run_fixed(const DevInstr *ins, int k, Ray &ray, 
 // bound by VALU issue.
 constexpr bool absorbs_only(int T) { return T == MXR_PHANTOM || T == kPhantomStep; }
 
-// All 64 lanes of a wave call it together (the exact phantom is walked by the
-// wave as a bundle); live: the lane holds a ray.  hit.live: the ray is to be
-// tallied.
+// BUNDLE: the phantom is walked by the wave as a bundle, and all 64 lanes call it
+// together; otherwise each ray walks by itself, KW crossings a round.  live: the
+// lane holds a ray.  hit.live: the ray is to be tallied.
 struct TallyHit {
     bool live;
     uint32_t ix, iy, ie;
@@ -326,7 +345,7 @@ struct TallyHit {
     double w;
 };
 
-template <bool EXACT, int KW, int... Ts>
+template <bool EXACT, bool BUNDLE, int KW, int... Ts>
 __device__ __forceinline__ TallyHit run_tallied(Chain<Ts...>, const DevInstr *ins, uint64_t ray_id, bool live,
                                                 const RunArgs &a, const double *mu_lds, uint32_t n_mat, uint32_t n_ebin) {
     Stream s;
@@ -363,18 +382,19 @@ __device__ __forceinline__ TallyHit run_tallied(Chain<Ts...>, const DevInstr *in
     to_local(ph, ray, q, dl);
     const double *mu_row = mu_lds + mu_row_of(ph, ray.E, n_ebin) * n_mat;
     double tau = 0.0;
-    double inv[3], a_in, a_out;
-    if constexpr (T[N - 2] == kPhantomStep) {
+    constexpr bool STEP = T[N - 2] == kPhantomStep;
+    if constexpr (BUNDLE) {
+        double inv[3], a_in, a_out;
         StepPath p{};
-        const bool in = live && step_path(phantom_geo(ph), q, dl, ph.par[3], (int)ph.aux[5], inv, a_in, a_out, p);
-        tau = bundle_tau<true, true>((const MXR_CONSTANT DevComp *)&ph, (const MXR_CONSTANT uint8_t *)ins->bricks, q, dl, inv,
-                                     a_in, a_out, in, mu_row, &p);
+        bool in = live;
+        if constexpr (STEP) in = in && step_path(phantom_geo(ph), q, dl, ph.par[3], (int)ph.aux[5], inv, a_in, a_out, p);
+        else in = in && volume_chord(phantom_geo(ph), q, dl, inv, a_in, a_out);
+        tau = bundle_tau<EXACT || STEP, STEP>((const MXR_CONSTANT DevComp *)&ph, (const MXR_CONSTANT uint8_t *)ins->bricks, q,
+                                              dl, inv, a_in, a_out, in, mu_row, &p);
         tau = in ? tau : 0.0;
-    } else {
-        const bool in = live && volume_chord(phantom_geo(ph), q, dl, inv, a_in, a_out);
-        tau = bundle_tau<EXACT>((const MXR_CONSTANT DevComp *)&ph, (const MXR_CONSTANT uint8_t *)ins->bricks, q, dl, inv, a_in, a_out, in,
-                                mu_row);
-        tau = in ? tau : 0.0;
+    } else if (live) {
+        if constexpr (STEP) tau = steps_tau((const MXR_CONSTANT DevComp *)&ph, phantom_geo(ph), q, dl, mu_row);
+        else tau = siddon_tau<EXACT, false, true, KW>(phantom_geo(ph), q, dl, mu_row);
     }
     if (live) {
         ray.w = ray.w * exp(-tau);
@@ -444,6 +464,12 @@ __device__ __forceinline__ uint64_t tile_of(uint32_t b, uint32_t order, uint32_t
 // coefficients of exp, sin, cos -- into registers for the whole kernel, which
 // costs occupancy.)  Which tiles of the ray range a work-group traces is
 // tile_of's choice (launch order unless the launch shape picks another).
+// Crossings per round of a ray's own walk: 5 where the occupancy leaves it the
+// registers for it (at 8 waves per SIMD it spills within the walk and the kernel
+// runs at 0.7 of its speed).
+template <int WAVES>
+constexpr int kRoundOf = WAVES == 7 ? 5 : kWalkRound;
+
 template <class C, bool LEDGER, bool TRACE, bool EXACT, int WAVES = WavesHint<C>::value>
 __global__ __launch_bounds__(kBlock, WAVES) void k_trace(const MXR_CONSTANT_PARAM DevInstr *__restrict__ insc,
                                                          RunArgs a) {
@@ -470,7 +496,11 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_trace(const MXR_CONSTANT_PARA
 
     const uint64_t logical = tile_of(blockIdx.x, a.xcd_order, a.blocks_per_xcd);
     const uint64_t i = logical * kBlock + threadIdx.x;
-    if (i < a.n) {
+    if constexpr (!LEDGER && !TRACE && ends_in_absorber(C{})) {
+        if (i < a.n)
+            tally_global(a, ins->c[ins->ncomp - 1].slot,
+                         run_tallied<EXACT, false, kRoundOf<WAVES>>(C{}, ins, a.first + i, true, a, mu_lds, n_mat, n_ebin));
+    } else if (i < a.n) {
         const uint64_t ray_id = TRACE ? a.ids[i] : a.first + i;
         Stream s;
         s.init(a.seed, ray_id, a.word3);
@@ -587,7 +617,7 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_image(const MXR_CONSTANT_PARA
         const TileRange &r = a.tp.r[ri];
         uint64_t ray_id;
         const bool live = tile_ray(r, at, t, lane, ray_id);
-        const TallyHit hit = run_tallied<EXACT, kWalkRound>(C{}, ins, ray_id, live, a, mu_lds, n_mat, n_ebin);
+        const TallyHit hit = run_tallied<EXACT, true, kWalkRound>(C{}, ins, ray_id, live, a, mu_lds, n_mat, n_ebin);
         if (!hit.live) continue;
         bool done = false;
         if (slots) {
@@ -847,7 +877,7 @@ __global__ __launch_bounds__(kBlock, BatchWavesHint<C>::value) void k_batch(cons
                 const bool live = r + threadIdx.x < r1;
                 const uint64_t ray_id = live ? r + threadIdx.x : r1 - 1;
                 tally_global(a, ins->c[ins->ncomp - 1].slot,
-                             run_tallied<EXACT, kWalkRound>(C{}, ins, ray_id, live, a, mu_lds, n_mat, n_ebin));
+                             run_tallied<EXACT, true, kWalkRound>(C{}, ins, ray_id, live, a, mu_lds, n_mat, n_ebin));
             }
         } else {
             for (uint64_t ray_id = r0 + threadIdx.x; ray_id < r1; ray_id += kBlock) {
@@ -869,8 +899,8 @@ __global__ __launch_bounds__(kBlock, BatchWavesHint<C>::value) void k_batch(cons
 // lane and no loop (the whole batch is one 2-D grid; the hardware dispatcher
 // balances the uneven jobs).  Tiles are numbered longest job first; within
 // groups of 8 x 64 consecutive tiles, each XCD gets 64 consecutive tiles.
-template <class C, bool EXACT>
-__global__ __launch_bounds__(kBlock, BatchWavesHint<C>::value) void k_batch_grid(const BatchJob *__restrict__ jobs,
+template <class C, bool EXACT, bool BUNDLE = true>
+__global__ __launch_bounds__(kBlock, BUNDLE ? BatchWavesHint<C>::value : RayWaves<C>::value) void k_batch_grid(const BatchJob *__restrict__ jobs,
                                                                           uint32_t n_jobs, uint64_t n_tiles) {
     extern __shared__ double smem[];
     constexpr uint64_t kRun = 64;
@@ -903,7 +933,7 @@ __global__ __launch_bounds__(kBlock, BatchWavesHint<C>::value) void k_batch_grid
     if constexpr (ends_in_absorber(C{})) {
         const uint64_t ray_id = id < a.n ? id : a.n - 1;  // every lane takes part
         tally_global(a, ins->c[ins->ncomp - 1].slot,
-                     run_tallied<EXACT, kWalkRound>(C{}, ins, ray_id, id < a.n, a, mu_lds, n_mat, n_ebin));
+                     run_tallied<EXACT, BUNDLE, kRoundOf<RayWaves<C>::value>>(C{}, ins, ray_id, id < a.n, a, mu_lds, n_mat, n_ebin));
     } else {
         if (id >= a.n) return;
         const LedgerLds L{nullptr};
@@ -929,20 +959,20 @@ __global__ __launch_bounds__(kBlock) void k_mu_energy_major(const double *T, uin
 // lane: the brick map (see DevInstr), the largest material id, and the box
 // of the voxels whose material differs from the corner voxel's.  out[0] =
 // largest id, out[1..3] = least x, y, z of such a voxel, out[4..6] = largest
-// x, y, z + 1, out[7] = the corner's material (out[1..3] start at ~0 and
-// out[0], out[4..6] at 0).  WORDS: rows of x start at multiples of four bytes,
+// x, y, z + 1, out[7] = the corner's material, out[8] = bricks of several
+// materials (out[1..3] start at ~0 and out[0], out[4..6], out[8] at 0).  WORDS: rows of x start at multiples of four bytes,
 // so a brick's row is one 32-bit load (a 512^3 volume in one pass of
 // neighbouring loads; a lane per row of single bytes took 584 us there).
 template <bool WORDS>
 __global__ __launch_bounds__(kBlock) void k_phantom_scan(const uint8_t *vol, uint32_t nx, uint32_t ny, uint32_t nz,
                                                         uint8_t *bricks, unsigned int *out) {
-    __shared__ unsigned int red[7];
-    if (threadIdx.x < 7) red[threadIdx.x] = (threadIdx.x >= 1 && threadIdx.x <= 3) ? ~0u : 0u;
+    __shared__ unsigned int red[8];
+    if (threadIdx.x < 8) red[threadIdx.x] = (threadIdx.x >= 1 && threadIdx.x <= 3) ? ~0u : 0u;
     __syncthreads();
     const uint32_t bg = vol[0];
     const uint32_t bx = (nx + 3) / 4, by = (ny + 3) / 4, bz = (nz + 3) / 4;
     const uint32_t n = bx * by * bz;  // at most 2^31 voxels and 2^20 + 9 layers: below 2^32
-    unsigned int mx = 0, lo[3] = {~0u, ~0u, ~0u}, hi[3] = {0u, 0u, 0u};
+    unsigned int mx = 0, mixed = 0, lo[3] = {~0u, ~0u, ~0u}, hi[3] = {0u, 0u, 0u};
     for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         const uint32_t x0 = (i % bx) * 4, y0 = (i / bx) % by * 4, z0 = i / bx / by * 4;
         const uint32_t x1 = x0 + 4 < nx ? x0 + 4 : nx, y1 = y0 + 4 < ny ? y0 + 4 : ny, z1 = z0 + 4 < nz ? z0 + 4 : nz;
@@ -973,8 +1003,10 @@ __global__ __launch_bounds__(kBlock) void k_phantom_scan(const uint8_t *vol, uin
                 }
             }
         bricks[i] = differ ? (uint8_t)255 : (uint8_t)m0;
+        mixed += differ != 0;
     }
     atomicMax(&red[0], mx);
+    if (mixed) atomicAdd(&red[7], mixed);
     if (hi[0] > 0)
         for (int d = 0; d < 3; ++d) {
             atomicMin(&red[1 + d], lo[d]);
@@ -983,6 +1015,7 @@ __global__ __launch_bounds__(kBlock) void k_phantom_scan(const uint8_t *vol, uin
     __syncthreads();
     if (threadIdx.x == 0) {
         atomicMax(out, red[0]);
+        atomicAdd(out + 8, red[7]);
         for (int d = 0; d < 3; ++d) {
             atomicMin(out + 1 + d, red[1 + d]);
             atomicMax(out + 4 + d, red[4 + d]);
@@ -1036,31 +1069,25 @@ typedef void (*KernelFn)(const MXR_CONSTANT_PARAM DevInstr *, RunArgs);
 
 template <class C, bool EXACT>
 struct KernelSet {
-    static KernelFn get(bool ledger, bool trace) {
+    // bundle: the image kernel, for chains that end in an absorbing phantom
+    static KernelFn get(bool ledger, bool trace, bool bundle = false) {
         if (trace) return ledger ? k_trace<C, true, true, EXACT> : k_trace<C, false, true, EXACT>;
         if (ledger) return k_trace<C, true, false, EXACT>;
         if constexpr (ends_in_absorber(C{}))
-            return k_image<C, EXACT>;
+            return bundle ? k_image<C, EXACT> : k_trace<C, false, false, EXACT, RayWaves<C>::value>;
         else
             return k_trace<C, false, false, EXACT>;
     }
-    // the plain run kernel compiled for another occupancy (waves per SIMD;
-    // 0: the chain's own)
+    // the plain run kernel, one ray a lane, compiled for another occupancy
+    // (waves per SIMD; 0: the chain's own; 4 is the image kernel's)
     static KernelFn plain(uint32_t waves) {
-        if constexpr (ends_in_absorber(C{})) {
-            switch (waves) {
-                case 4: return k_image<C, EXACT, 4>;
-                case 6: return k_image<C, EXACT, 6>;
-                case 8: return k_image<C, EXACT, 8>;
-                default: return k_image<C, EXACT>;
-            }
-        } else {
-            switch (waves) {
-                case 4: return k_trace<C, false, false, EXACT, 4>;
-                case 6: return k_trace<C, false, false, EXACT, 6>;
-                case 8: return k_trace<C, false, false, EXACT, 8>;
-                default: return k_trace<C, false, false, EXACT>;
-            }
+        switch (waves) {
+            case 4:
+                if constexpr (ends_in_absorber(C{})) return get(false, false, true);
+                else return k_trace<C, false, false, EXACT, 4>;
+            case 6: return k_trace<C, false, false, EXACT, 6>;
+            case 8: return k_trace<C, false, false, EXACT, 8>;
+            default: return get(false, false);
         }
     }
 };
@@ -1084,14 +1111,14 @@ enum RunMode { kModePlain = 0, kModeProposal, kModeCollect, kModeProposalCollect
 
 // exact: the phantom's planes are reached exactly by adding the voxel edge
 // (chains without a phantom ignore it)
-KernelFn pick_kernel(int recipe, bool ledger, bool trace, bool exact, int mode) {
+KernelFn pick_kernel(int recipe, bool ledger, bool trace, bool exact, int mode, bool bundle) {
     if (mode != kModePlain) {
         if (recipe == kRecipeEdct && mode == kModeProposal)
-            return exact ? KernelSet<ChainEdctProposal, true>::get(ledger, trace)
-                         : KernelSet<ChainEdctProposal, false>::get(ledger, trace);
+            return exact ? KernelSet<ChainEdctProposal, true>::get(ledger, trace, bundle)
+                         : KernelSet<ChainEdctProposal, false>::get(ledger, trace, bundle);
         if (recipe == kRecipeEdct && mode == kModeCollect && !trace)
-            return exact ? KernelSet<ChainEdctCollect, true>::get(ledger, false)
-                         : KernelSet<ChainEdctCollect, false>::get(ledger, false);
+            return exact ? KernelSet<ChainEdctCollect, true>::get(ledger, false, bundle)
+                         : KernelSet<ChainEdctCollect, false>::get(ledger, false, bundle);
         // any other combination (e.g. a proposal while collecting) dispatches
         // both on the run's arguments
         return exact ? KernelSet<ChainGeneric, true>::get(ledger, trace) : KernelSet<ChainGeneric, false>::get(ledger, trace);
@@ -1099,16 +1126,19 @@ KernelFn pick_kernel(int recipe, bool ledger, bool trace, bool exact, int mode) 
     switch (recipe) {
         case kRecipeBasic: return KernelSet<ChainBasic, true>::get(ledger, trace);
         case kRecipeEdct:
-            return exact ? KernelSet<ChainEdct, true>::get(ledger, trace) : KernelSet<ChainEdct, false>::get(ledger, trace);
+            return exact ? KernelSet<ChainEdct, true>::get(ledger, trace, bundle)
+                         : KernelSet<ChainEdct, false>::get(ledger, trace, bundle);
         case kRecipeBeamline: return KernelSet<ChainBeamline, true>::get(ledger, trace);
-        case kRecipeEdctStep: return KernelSet<ChainEdctStep, true>::get(ledger, trace);
+        case kRecipeEdctStep: return KernelSet<ChainEdctStep, true>::get(ledger, trace, bundle);
         case kRecipeCrl: return KernelSet<ChainCrl, true>::get(ledger, trace);
         case kRecipeEdctScatter:
+            if (bundle && !ledger && !trace)
+                return exact ? k_trace<ChainEdctScatterOnce, false, false, true> : k_trace<ChainEdctScatterOnce, false, false, false>;
             return exact ? KernelSet<ChainEdctScatter, true>::get(ledger, trace)
                          : KernelSet<ChainEdctScatter, false>::get(ledger, trace);
         case kRecipeEdctAimed:
             // plain runs only; ledgers and ray traces take the generic chain
-            if (exact && !ledger && !trace) return k_image<ChainEdctAimed, true>;
+            if (exact && !ledger && !trace) return KernelSet<ChainEdctAimed, true>::get(false, false, bundle);
             return exact ? KernelSet<ChainGeneric, true>::get(ledger, trace)
                          : KernelSet<ChainGeneric, false>::get(ledger, trace);
         default:
@@ -1117,11 +1147,16 @@ KernelFn pick_kernel(int recipe, bool ledger, bool trace, bool exact, int mode) 
     }
 }
 
-// whether pick_kernel's choice is an image kernel (launched by tiles)
-bool is_image_kernel(int recipe, bool ledger, bool trace, bool exact, int mode) {
+// whether a run has a form that walks the phantom as bundles, and whether that is
+// an image kernel (launched by tiles)
+bool has_image_kernel(int recipe, bool ledger, bool trace, bool exact, int mode) {
     if (ledger || trace) return false;
     if (mode == kModePlain) return recipe == kRecipeEdct || recipe == kRecipeEdctStep || (recipe == kRecipeEdctAimed && exact);
     return recipe == kRecipeEdct && (mode == kModeProposal || mode == kModeCollect);
+}
+bool has_bundle_walk(int recipe, bool ledger, bool trace, bool exact, int mode) {
+    return has_image_kernel(recipe, ledger, trace, exact, mode) ||
+           (!ledger && !trace && mode == kModePlain && recipe == kRecipeEdctScatter);
 }
 
 // the compacting kernel for plain runs of a chain with a compaction prefix,
@@ -1137,10 +1172,12 @@ KernelFn pick_compact(int recipe) {
 typedef void (*BatchKernelFn)(const BatchJob *, uint32_t, uint64_t, uint32_t, unsigned long long *);
 typedef void (*BatchGridFn)(const BatchJob *, uint32_t, uint64_t);
 
-BatchGridFn pick_batch_grid(int recipe, bool exact) {
+BatchGridFn pick_batch_grid(int recipe, bool exact, bool bundle) {
     switch (recipe) {
         case kRecipeBasic: return k_batch_grid<ChainBasic, true>;
-        case kRecipeEdct: return exact ? k_batch_grid<ChainEdct, true> : k_batch_grid<ChainEdct, false>;
+        case kRecipeEdct:
+            if (!bundle) return exact ? k_batch_grid<ChainEdct, true, false> : k_batch_grid<ChainEdct, false, false>;
+            return exact ? k_batch_grid<ChainEdct, true> : k_batch_grid<ChainEdct, false>;
         case kRecipeBeamline: return k_batch_grid<ChainBeamline, true>;
         default: return exact ? k_batch_grid<ChainGeneric, true> : k_batch_grid<ChainGeneric, false>;
     }
@@ -1219,6 +1256,14 @@ mxr_status set_error(mxr_status st, const char *msg) {
 }
 }  // namespace mxr_host
 
+// What decides whether a projection's waves walk the phantom as bundles.
+struct BundleView {
+    double layers = 0.0;  // of the occupied box, across the cone's axis
+    double cone = 0.0;    // voxels that the whole cone spans at the phantom
+    double mixed = 0.0;   // share of the box's bricks that hold several materials
+    double steps = 1.0;   // steps per voxel (fixed-step model), else 1
+};
+
 struct mxr_instrument {
     mxr_launch_shape shape{0, 1, 0, 0};  // plain runs' launch shape (see mxr_set_launch_shape)
     uint32_t order = 0;                  // XCD order of the other runs (see tile_of)
@@ -1234,6 +1279,7 @@ struct mxr_instrument {
     double *mu_dev;       // the phantom's staged attenuation table and brick map (device), or null
     PropTable prop_host;  // its host copy (branch sizes are set per run)
     bool prop_on;
+    BundleView view;      // the phantom as a projection's waves meet it
 };
 
 // Derive per-component constants on the host (glibc), validate ranges.
@@ -1431,6 +1477,29 @@ static void proposal_box(const DevComp &c, double lo[3], double hi[3]) {
     hi[2] = c.par[2];
 }
 
+// A phantom's view: its occupied box [lo, hi) in voxels, of which `mixed` bricks
+// hold several materials, from the instrument's cone-beam source.
+static BundleView bundle_view(const DevInstr &d, const unsigned *lo, const unsigned *hi, unsigned mixed) {
+    BundleView v;
+    const DevComp &src = d.c[0], &ph = d.c[d.phantom];
+    if (src.type != MXR_SRC_CONE_BEAM) return v;
+    // the cone's axis in the phantom's frame, and the way to the phantom's centre
+    double along[3], way = 0.0, bricks = 1.0;
+    int axis = 0;
+    for (int i = 0; i < 3; ++i) {
+        along[i] = 0.0;
+        for (int j = 0; j < 3; ++j) along[i] += ph.rot[3 * i + j] * src.rot[6 + j];
+        if (std::fabs(along[i]) > std::fabs(along[axis])) axis = i;
+        way += (ph.pos[i] - src.pos[i]) * (ph.pos[i] - src.pos[i]);
+        bricks *= (double)((hi[i] + 3) / 4 - lo[i] / 4);
+    }
+    v.layers = (double)(hi[axis] - lo[axis]);
+    v.cone = 2.0 * std::tan(std::min(src.par[0], 1.5)) * std::sqrt(way) / ph.par[0];
+    v.mixed = (double)mixed / bricks;
+    if (ph.flags & 1u) v.steps = ph.par[0] / ph.par[3];
+    return v;
+}
+
 extern "C" {
 
 uint32_t mxr_abi_version(void) { return MXR_ABI_VERSION; }
@@ -1526,7 +1595,7 @@ mxr_status mxr_instrument_create(const mxr_instrument_desc *desc, mxr_instrument
         // one pass over the volume: every material id must index the mu
         // table, and the box of voxels unlike the corner bounds the walk
         DevComp &c = d.c[d.phantom];
-        unsigned int *dscan = nullptr, hs[8] = {0u, ~0u, ~0u, ~0u, 0u, 0u, 0u, 0u};
+        unsigned int *dscan = nullptr, hs[9] = {0u, ~0u, ~0u, ~0u, 0u, 0u, 0u, 0u, 0u};
         e = hipMalloc((void **)&dscan, sizeof hs);
         if (e == hipSuccess) e = hipMemcpy(dscan, hs, sizeof hs, hipMemcpyHostToDevice);
         if (e == hipSuccess) {
@@ -1557,6 +1626,7 @@ mxr_status mxr_instrument_create(const mxr_instrument_desc *desc, mxr_instrument
         }
         c.aux[14] = (double)hs[7];
         c.aux[15] = any ? 1.0 : 0.0;
+        if (any) ins->view = bundle_view(d, hs + 1, hs + 4, hs[8]);
     }
     e = hipMalloc((void **)&ins->dev, sizeof(DevInstr));
     if (e != hipSuccess) {
@@ -1639,16 +1709,40 @@ static hipError_t launch_tiles(KernelFn k, const DevInstr *dev, RunArgs a, size_
     return hipSuccess;
 }
 
-// Whether a proposal run takes the event walk, one ray a lane at 8 waves per
-// SIMD, rather than the image kernel: its rays nearly all reach the monitor, so
-// the bundle's 4 waves have to pay by the walk alone.  They do not below 2^19
-// rays (one round of the chip; 16 replicas of 3.6e5 rays, 93^3: 885 us so, 1088
-// by tiles), nor in small phantoms before the tiles are large enough for a
-// private histogram (2e6 rays, 47^3 / 93^3: 2388 / 3088 us, tiles 2735 / 3862;
-// 171^3 / 240^3: 4805 / 7253 and 4436 / 4612).
-static bool small_proposal(const DevInstr &d, uint64_t n) {
-    const uint32_t *dims = d.c[1].dims;
-    return n < (1ull << 19) || (n < (1ull << 23) && std::max({dims[0], dims[1], dims[2]}) < 128);
+// Whether rays [a.first, a.first + a.n) of a run walk the phantom as bundles (the
+// image kernel, in tiles; scattered photons' primary chords) rather than each by
+// itself (k_trace, whose waves hold half the registers and whose launch has no
+// tiles to find).  n: the rays of all jobs that are traced together; tiles: a
+// launch has them (a batch's grid does not).
+//   - Bundles pay by the layers they skip, so not where a wave's rays spread over
+//     kBundleNarrow voxels or nearly every brick holds a boundary (1e7 rays
+//     through 256^3 voxels of noise: bundles 1400 us, rays 710).
+//   - They pay from about 2^35 layer pairs of rays on: 3e5 / 1e6 rays through
+//     the 256^3 phantom's 250 layers 77 / 84 us, rays 73 / 127; 1e6 / 3e6 through
+//     128^3 64 / 115 and 60 / 115; with a monitor that sees the whole cone 1e5 /
+//     3e5, 256^3: 96 / 116 and 92 / 140.  Steps count for layers, and two or more
+//     to a voxel pay at once (1e4 rays, 64^3, a third of a voxel: 23.4 us, 27.2).
+//   - From 2^23 rays on the tiles have a private histogram, which pays for
+//     itself: 1e7 rays, 64^3: 171 us, 307.
+//   - Photons scattered once: two of their three chords, if the last one is
+//     aimed (not aimed, 1e7 rays: 23.8 ms, by rays 14.5); 1e5 / 3e5 / 1e6 rays
+//     371 / 661 / 1072 us, by rays 357 / 658 / 1373.  Scattered twice, two of five:
+//     the lower occupancy costs the others more than it gains (2e7 rays 58.4 and
+//     53.2 ms).
+static bool walks_as_bundle(const mxr_instrument *ins, const RunArgs &a, uint64_t n, bool tiles = true) {
+    const BundleView &v = ins->view;
+    const double c = (double)a.n_total / (double)a.G2;  // rays per source cell
+    const bool whole = a.first == 0 && a.n == a.n_total;
+    const double spread = c >= 64.0 ? 1.0 : whole ? std::sqrt(64.0 / c) : 64.0 / c;  // cells of a wave, across
+    if (v.layers >= (double)kBundleLayers && v.mixed > 0.75) return false;
+    if (!a.prop && v.cone / (double)a.G * spread > (double)kBundleNarrow) return false;
+    if (ins->recipe == kRecipeEdctScatter) {
+        const DevComp &ph = ins->host.c[1];
+        return ph.par[4] == 1.0 && (ph.flags & 4u) && n >= (1ull << 18);
+    }
+    if (v.steps >= 2.0) return true;
+    const double looks = v.layers * v.steps;
+    return (tiles && n >= (1ull << 23)) || (double)n * looks * looks >= 0x1p35;
 }
 
 static mxr_status launch(mxr_instrument *ins, const RunArgs &base, uint64_t n, bool ledger, bool trace,
@@ -1657,22 +1751,17 @@ static mxr_status launch(mxr_instrument *ins, const RunArgs &base, uint64_t n, b
     const int mode = base.hits.count ? (base.prop ? kModeProposalCollect : kModeCollect)
                                      : (base.prop ? kModeProposal : kModePlain);
     const bool plain = !ledger && !trace && mode == kModePlain;
-    KernelFn k = pick_kernel(ins->recipe, ledger, trace, exact, mode);
-    if (plain && ins->shape.occupancy) {
+    bool bundle = has_bundle_walk(ins->recipe, ledger, trace, exact, mode);
+    if (bundle && plain && ins->shape.occupancy)
+        bundle = ins->shape.occupancy == 4 && (ins->recipe != kRecipeEdctScatter || ins->host.c[1].par[4] == 1.0);
+    else if (bundle)
+        bundle = walks_as_bundle(ins, base, n);
+    KernelFn k = pick_kernel(ins->recipe, ledger, trace, exact, mode, bundle);
+    if (plain && ins->shape.occupancy && !bundle) {
         KernelFn ko = pick_plain(ins->recipe, exact, ins->shape.occupancy);
         if (ko) k = ko;
     }
-    // photons scattered once walk two of their three chords as a bundle, 18.7 ->
-    // 14.4 ms for 2e7 rays through 256^3; scattered twice, two of five, and the
-    // lower occupancy costs the other three more than it gains (53.2 -> 58.4 ms)
-    if (plain && ins->recipe == kRecipeEdctScatter && ins->host.c[1].par[4] == 1.0 &&
-        (ins->shape.occupancy == 0 || ins->shape.occupancy == 4))
-        k = exact ? k_trace<ChainEdctScatterOnce, false, false, true> : k_trace<ChainEdctScatterOnce, false, false, false>;
-    const bool small = mode == kModeProposal && ins->recipe == kRecipeEdct && !ledger && !trace &&
-                       small_proposal(ins->host, n);
-    if (small)
-        k = exact ? k_trace<ChainEdctProposal, false, false, true, 8> : k_trace<ChainEdctProposal, false, false, false, 8>;
-    if (!small && is_image_kernel(ins->recipe, ledger, trace, exact, mode)) {
+    if (bundle && has_image_kernel(ins->recipe, ledger, trace, exact, mode)) {
         RunArgs a = base;
         a.xcd_order = plain ? ins->shape.xcd_order : ins->order;
         plan_tiles(a, ins->host, base.prop ? &ins->prop_host : nullptr);
@@ -2111,10 +2200,11 @@ struct mxr_batch {
     uint32_t n_jobs;
     uint64_t total_rays, total_cost;
     std::vector<BatchJob> host_jobs;          // longest-first
-    std::vector<const DevInstr *> host_ins;  // their instruments' constants (host)
+    std::vector<const mxr_instrument *> host_ins;
     BatchJob *dev_jobs;
     unsigned long long *counter;
     size_t shmem;
+    bool bundle;               // whether the grid form walks phantoms as bundles
     mxr_batch_schedule sched;  // normalised launch shape
     uint64_t n_tiles;
     int n_cu;
@@ -2232,17 +2322,17 @@ static mxr_status batch_capture(mxr_batch *b) {
         // jobs dealt longest-first round-robin over the branches, which fork
         // from and join back into the capture stream
         const uint32_t nb = b->sched.branches;
-        KernelFn k = pick_kernel(b->recipe, false, false, b->exact, kModePlain);
         launch_err = hipEventRecord(b->fork, b->capture_stream);
         for (uint32_t i = 0; launch_err == hipSuccess && i < nb; ++i)
             launch_err = hipStreamWaitEvent(b->branch[i], b->fork, 0);
-        const bool image = is_image_kernel(b->recipe, false, false, b->exact, kModePlain);
         for (uint32_t j = 0; launch_err == hipSuccess && j < b->n_jobs; ++j) {
             RunArgs a = b->host_jobs[j].args;
-            if (image) {
-                const DevInstr &d = *b->host_ins[j];
-                plan_tiles(a, d, nullptr);
-                launch_err = launch_tiles(k, a.ins, a, image_lds(a, d), b->branch[j % nb]);
+            const mxr_instrument *ins = b->host_ins[j];
+            const bool bundle = has_bundle_walk(b->recipe, false, false, b->exact, kModePlain) && walks_as_bundle(ins, a, a.n);
+            const KernelFn k = pick_kernel(b->recipe, false, false, b->exact, kModePlain, bundle);
+            if (bundle && has_image_kernel(b->recipe, false, false, b->exact, kModePlain)) {
+                plan_tiles(a, ins->host, nullptr);
+                launch_err = launch_tiles(k, a.ins, a, image_lds(a, ins->host), b->branch[j % nb]);
             } else {
                 launch_err = launch_job(k, a, b->shmem, b->branch[j % nb]);
             }
@@ -2256,7 +2346,7 @@ static mxr_status batch_capture(mxr_batch *b) {
         const uint64_t groups = (b->n_tiles + 511) / 512 * 512;
         const uint32_t gx = (uint32_t)std::min<uint64_t>(groups, 1u << 16);
         const uint32_t gy = (uint32_t)((groups + gx - 1) / gx);
-        hipLaunchKernelGGL(pick_batch_grid(b->recipe, b->exact), dim3(gx, gy), dim3(kBlock), b->shmem,
+        hipLaunchKernelGGL(pick_batch_grid(b->recipe, b->exact, b->bundle), dim3(gx, gy), dim3(kBlock), b->shmem,
                            b->capture_stream, (const BatchJob *)b->dev_jobs, b->n_jobs, b->n_tiles);
     } else {
         hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(1), 0, b->capture_stream, b->counter);
@@ -2369,10 +2459,13 @@ mxr_status mxr_batch_create(const mxr_batch_job *jobs, uint32_t n_jobs, const mx
     b->n_jobs = n_jobs;
     b->total_rays = total_rays;
     b->total_cost = total_cost;
+    uint64_t bundle_cost = 0;
     for (const auto &o : order) {
+        if (walks_as_bundle(jobs[o.second].instrument, hj[o.second].args, total_rays, false)) bundle_cost += o.first;
         b->host_jobs.push_back(hj[o.second]);
-        b->host_ins.push_back(&jobs[o.second].instrument->host);
+        b->host_ins.push_back(jobs[o.second].instrument);
     }
+    b->bundle = bundle_cost >= total_cost - bundle_cost;
     e = hipDeviceGetAttribute(&b->n_cu, hipDeviceAttributeMultiprocessorCount, cur);
     if (e != hipSuccess || b->n_cu < 1) b->n_cu = 256;
     // one launch per job, one branch, until tuned

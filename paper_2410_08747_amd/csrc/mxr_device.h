@@ -1558,6 +1558,31 @@ __device__ __forceinline__ void stretch_steps(const MXR_CONSTANT DevComp *ph, co
     }
 }
 
+// Optical depth of one path by its steps, the sums of step_tau; only the steps in
+// the occupied box's layers across the path's dominant axis look at voxels.
+__device__ __forceinline__ double steps_tau(const MXR_CONSTANT DevComp *ph, const PhantomGeo &g, const double q[3],
+                                            const double dl[3], const double *__restrict__ mu_row) {
+    double inv[3], a_in, a_out;
+    StepPath p;
+    if (!step_path(g, q, dl, ph->par[3], (int)ph->aux[5], inv, a_in, a_out, p)) return 0.0;
+    OpenRun run;
+    run.m = g.bg, run.mu = mu_row[g.bg], run.a_start = a_in, run.tau = 0.0;
+    if (g.box) {
+        const double ax = fabs(dl[0]), ay = fabs(dl[1]), az = fabs(dl[2]);
+        const int D = (ax >= ay && ax >= az) ? 0 : (ay >= az ? 1 : 2);
+        const bool back = pick3(D, dl[0], dl[1], dl[2]) < 0.0;
+        const double c = pick3(D, g.corner[0], g.corner[1], g.corner[2]);
+        const int lo = (int)rint((pick3(D, g.blo[0], g.blo[1], g.blo[2]) - c) * g.rv);
+        const int hi = (int)rint((pick3(D, g.bhi[0], g.bhi[1], g.bhi[2]) - c) * g.rv);
+        const int end = back ? 0 : pick3(D, g.n[0], g.n[1], g.n[2]);
+        const double u0 = pick3(D, p.u0[0], p.u0[1], p.u0[2]), du = pick3(D, p.du[0], p.du[1], p.du[2]);
+        const int js = step_at(back ? hi : lo, back, end, u0, du, p.J), je = step_at(back ? lo : hi, back, end, u0, du, p.J);
+        if (je > js) stretch_steps(ph, p, js, je, a_in, a_out, run, mu_row);
+        if (run.m != g.bg) turn_run(run, a_in + (double)(je - 1) * p.h, a_out, g.bg, mu_row);
+    }
+    return add_run(run.mu, a_out - run.a_start, run.tau);
+}
+
 // Code of a footprint of (da + 1) x (db + 1) cells from offset o on, strides
 // strA and strB: the four corners first, the cells between them where the
 // corners agree (all loads in flight; offsets beyond the footprint fall on its
