@@ -303,10 +303,11 @@ mxr_status mxr_set_launch_shape(mxr_instrument *ins, const mxr_launch_shape *sha
  * is free; the kernels' occupancy and ray order are the levers measured
  * here): times each candidate shape -- occupancy 0/4/6/8 for fixed chains,
  * both XCD ray orders, and for chains with a crop after the source the
- * compacting kernel at 64 or 16 rounds or none -- on rays [0, n) of an
- * n_total-ray run, n = max(1, rays_fraction n_total), after one untimed run
- * each; keeps the fastest and records it under a key of the instrument
- * (component chain, exactness of the phantom's planes, phantom and monitor
+ * compacting kernel at 64 or 16 rounds or none -- on whole runs of n =
+ * max(1, rays_fraction n_total) rays (projections, for n < n_total, in the
+ * form that n_total rays take), after one untimed run each; keeps the fastest
+ * and records it under a key of the instrument (the kernels' version,
+ * component chain, exactness of the phantom's planes, phantom and monitor
  * sizes, the run size's power of two) in the text file cache_path
  * (nullable), which later calls consult before timing anything.  The chosen
  * shape is set on the instrument and returned in out (nullable).  The

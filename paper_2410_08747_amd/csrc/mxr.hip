@@ -2068,10 +2068,15 @@ mxr_status mxr_set_launch_shape(mxr_instrument *ins, const mxr_launch_shape *sha
     return MXR_OK;
 }
 
+// Part of every tuning-cache key: what a cached shape or schedule selects.  It
+// counts up whenever a shape's kernel, or the default one, is replaced: a shape
+// tuned on other kernels is then tuned anew instead of picking a slow one.
+static const char *kTuneVersion = "kernels 3 ";
+
 // Tuning-cache key of an instrument's plain runs of about n_total rays.
 static std::string instrument_key(const mxr_instrument *ins, uint64_t n_total) {
     const DevInstr &d = ins->host;
-    std::string k = "instrument recipe " + std::to_string(ins->recipe) + " chain";
+    std::string k = std::string(kTuneVersion) + "instrument recipe " + std::to_string(ins->recipe) + " chain";
     for (uint32_t c = 0; c < d.ncomp; ++c) {
         k += " " + std::to_string(d.c[c].type) + "/" + std::to_string(d.c[c].flags);
         if (d.c[c].type == MXR_PHANTOM || d.c[c].type == MXR_DETECTOR)
@@ -2116,8 +2121,22 @@ mxr_status mxr_autotune_instrument(mxr_instrument *ins, uint64_t n_total, double
     const bool fixed = pick_plain(ins->recipe, true, 0) != nullptr;
     const bool compactable = pick_compact(ins->recipe) != nullptr;
     std::vector<mxr_launch_shape> cand;
+    const uint64_t n = std::max<uint64_t>(1, (uint64_t)((double)n_total * rays_fraction));
+    // which form a projection takes depends on its size, so a part of the rays
+    // is timed in the form that all of them take
+    bool forms = false, bundle = false;
+    if (n < n_total) {
+        RunArgs a;
+        const mxr_status st = common_args(ins, n_total, 1, 0, 0, a);
+        if (st != MXR_OK) return st;
+        a.n = n_total;
+        const bool exact = ins->host.phantom < 0 || ins->host.c[ins->host.phantom].aux[4] != 0.0;
+        forms = has_bundle_walk(ins->recipe, false, false, exact, kModePlain);
+        bundle = forms && walks_as_bundle(ins, a, n_total);
+    }
     for (uint32_t occ : {0u, 4u, 6u, 8u}) {
         if (occ && !fixed) continue;
+        if (forms && (occ == 0 || (occ == 4) != bundle)) continue;
         for (uint32_t xo : {0u, 1u, 2u}) {
             if (compactable) {
                 cand.push_back({occ, 1, 0, xo});
@@ -2126,7 +2145,6 @@ mxr_status mxr_autotune_instrument(mxr_instrument *ins, uint64_t n_total, double
             cand.push_back({occ, 0, 0, xo});
         }
     }
-    const uint64_t n = std::max<uint64_t>(1, (uint64_t)((double)n_total * rays_fraction));
     const mxr_launch_shape saved = ins->shape;
     hipStream_t st = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -2142,7 +2160,7 @@ mxr_status mxr_autotune_instrument(mxr_instrument *ins, uint64_t n_total, double
         for (int rep = 0; status == MXR_OK && rep < 2; ++rep) {  // the first run warms up
             e = hipEventRecord(e0, st);
             if (e == hipSuccess)
-                status = mxr_run(ins, 0, n, n_total, 1, 0, 0, tallies, n_tallies, nullptr, st);
+                status = mxr_run(ins, 0, n, n, 1, 0, 0, tallies, n_tallies, nullptr, st);  // a whole run: a part of one has no tiles
             if (status == MXR_OK) {
                 e = hipEventRecord(e1, st);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -2201,6 +2219,7 @@ struct mxr_batch {
     uint64_t total_rays, total_cost;
     std::vector<BatchJob> host_jobs;          // longest-first
     std::vector<const mxr_instrument *> host_ins;
+    std::vector<bool> host_bundle;            // whether a job's own launch walks its phantom as bundles
     BatchJob *dev_jobs;
     unsigned long long *counter;
     size_t shmem;
@@ -2328,7 +2347,7 @@ static mxr_status batch_capture(mxr_batch *b) {
         for (uint32_t j = 0; launch_err == hipSuccess && j < b->n_jobs; ++j) {
             RunArgs a = b->host_jobs[j].args;
             const mxr_instrument *ins = b->host_ins[j];
-            const bool bundle = has_bundle_walk(b->recipe, false, false, b->exact, kModePlain) && walks_as_bundle(ins, a, a.n);
+            const bool bundle = b->host_bundle[j];
             const KernelFn k = pick_kernel(b->recipe, false, false, b->exact, kModePlain, bundle);
             if (bundle && has_image_kernel(b->recipe, false, false, b->exact, kModePlain)) {
                 plan_tiles(a, ins->host, nullptr);
@@ -2464,6 +2483,8 @@ mxr_status mxr_batch_create(const mxr_batch_job *jobs, uint32_t n_jobs, const mx
         if (walks_as_bundle(jobs[o.second].instrument, hj[o.second].args, total_rays, false)) bundle_cost += o.first;
         b->host_jobs.push_back(hj[o.second]);
         b->host_ins.push_back(jobs[o.second].instrument);
+        b->host_bundle.push_back(has_bundle_walk(b->recipe, false, false, b->exact, kModePlain) &&
+                                 walks_as_bundle(jobs[o.second].instrument, hj[o.second].args, hj[o.second].args.n));
     }
     b->bundle = bundle_cost >= total_cost - bundle_cost;
     e = hipDeviceGetAttribute(&b->n_cu, hipDeviceAttributeMultiprocessorCount, cur);
@@ -2474,10 +2495,10 @@ mxr_status mxr_batch_create(const mxr_batch_job *jobs, uint32_t n_jobs, const mx
         delete b;
         return fail(MXR_E_INVALID, "%s", kScheduleRule);
     }
-    char key[256];
+    char key[320];
     std::string chain;
     for (uint32_t c = 0; c < i0->host.ncomp; ++c) chain += std::to_string(i0->host.c[c].type) + (c + 1 < i0->host.ncomp ? "-" : "");
-    snprintf(key, sizeof key, "chain=%s jobs=%u rays=%llu cost=%llu cu=%d", chain.c_str(), n_jobs,
+    snprintf(key, sizeof key, "%schain=%s jobs=%u rays=%llu cost=%llu cu=%d", kTuneVersion, chain.c_str(), n_jobs,
              (unsigned long long)total_rays, (unsigned long long)total_cost, b->n_cu);
     b->key = key;
     b->graph_ready = false;
