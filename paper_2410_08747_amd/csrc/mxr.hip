@@ -608,8 +608,10 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_image(const MXR_CONSTANT_PARA
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t turns = 4u << a.tp.rounds;         // a wave's worth of rays, of the tile
+    // the kernel's second argument, where its alignment puts it behind the first
+    constexpr size_t kArgsAt = (sizeof(void *) + alignof(RunArgs) - 1) / alignof(RunArgs) * alignof(RunArgs);
     const MXR_CONSTANT RunArgs *args =
-        (const MXR_CONSTANT RunArgs *)((const MXR_CONSTANT char *)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(void *));
+        (const MXR_CONSTANT RunArgs *)((const MXR_CONSTANT char *)__builtin_amdgcn_kernarg_segment_ptr() + kArgsAt);
     const uint32_t slot0 = det.slot;
     for (uint32_t t = wave; t < turns; t += kBlock / 64) {
         const DevInstr *ins = (const DevInstr *)again((const MXR_CONSTANT DevInstr *)insc);
