@@ -248,8 +248,9 @@ void mxr_instrument_destroy(mxr_instrument *ins);
  *              its rounds); 0: one ray per lane
  *   rounds     compacting kernel: 64-ray rounds per wave, 1..64 (0 = 64)
  *   xcd_order  which ray tiles (256 rays; in bundles up to 4096) each of
- *              the eight XCDs traces: 0, the i-th XCD the i-th eighth of the ray range; 1, launch order;
- *              2, runs of 64 consecutive tiles dealt to the XCDs in turn.
+ *              the eight XCDs traces: 0, the i-th XCD the i-th eighth of the
+ *              ray range; 1, launch order; 2, runs of 64 consecutive tiles
+ *              dealt to the XCDs in turn.
  *              The default is 1 for instruments with a phantom (the
  *              stratified source sends each block of ray ids through one
  *              band of the cone, so order 0 leaves XCDs idle where the
@@ -263,6 +264,11 @@ typedef struct {
     uint32_t rounds;
     uint32_t xcd_order;
 } mxr_launch_shape;
+
+/* Zeroes the arrays of tallies[0 .. n_tallies) in one launch (up to
+ * MXR_MAX_DETECTORS tallies).  (Library bookkeeping: the monitors start empty.)
+ * Errors: MXR_E_INVALID (null tallies or arrays, too many tallies), MXR_E_HIP. */
+mxr_status mxr_tally_clear(const mxr_tally *tallies, uint32_t n_tallies, void *hip_stream);
 
 /* Traces rays [first_ray, first_ray + n_rays) of an n_total-ray run and
  * adds their histograms into tallies[0 .. n_tallies) (one per monitor, in

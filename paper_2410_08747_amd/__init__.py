@@ -168,6 +168,8 @@ def _load() -> ctypes.CDLL:
         ctypes.c_void_p,
     ]
     lib.mxr_run.restype = ctypes.c_int
+    lib.mxr_tally_clear.argtypes = [ctypes.POINTER(mxr_tally), ctypes.c_uint32, ctypes.c_void_p]
+    lib.mxr_tally_clear.restype = ctypes.c_int
     lib.mxr_trace_rays.argtypes = [
         ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint64,
         ctypes.c_uint32, ctypes.c_uint32, ctypes.POINTER(mxr_ray_soa), ctypes.c_void_p,
@@ -270,6 +272,11 @@ def mxr_instrument_create(desc: mxr_instrument_desc) -> int:
 
 def mxr_instrument_destroy(handle: int) -> None:
     lib.mxr_instrument_destroy(handle)
+
+
+def mxr_tally_clear(tallies: Sequence[mxr_tally], stream=None) -> None:
+    arr = (mxr_tally * max(1, len(tallies)))(*tallies)
+    _check(lib.mxr_tally_clear(arr, len(tallies), _stream_handle(stream)))
 
 
 def mxr_run(handle: int, first_ray: int, n_rays: int, n_total: int, seed: int, purpose: int, job: int,
@@ -568,9 +575,15 @@ class Instrument:
         out = []
         for d in self.detectors:
             nb = int(d["nx"]) * int(d["ny"]) * int(d["ne"])
-            # one allocation and one fill for the three
-            count, sum_w, sum_w2 = torch.zeros(3, nb, dtype=torch.float64, device=self.device).unbind(0)
-            out.append({"count": count.view(torch.int64), "sum_w": sum_w, "sum_w2": sum_w2})
+            # an allocation each: a histogram is kept, saved and updated by itself
+            out.append({"count": torch.empty(nb, dtype=torch.int64, device=self.device),
+                        "sum_w": torch.empty(nb, dtype=torch.float64, device=self.device),
+                        "sum_w2": torch.empty(nb, dtype=torch.float64, device=self.device)})
+        if torch.cuda.current_device() == self.device.index:
+            mxr_tally_clear(self.tally_structs(out))
+        else:
+            with torch.cuda.device(self.device):
+                mxr_tally_clear(self.tally_structs(out))
         return out
 
     @staticmethod

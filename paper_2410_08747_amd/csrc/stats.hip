@@ -1,4 +1,4 @@
-// stats.hip -- per-bin statistics of replicated runs.
+// stats.hip -- histograms: clearing, and per-bin statistics of replicated runs.
 //
 // The error of a Monte Carlo detector image is estimated by batch means:
 // R independent replicas (runs on disjoint random streams) give R estimates
@@ -38,7 +38,46 @@ __global__ void k_batch_means(const double *sums, uint32_t R, uint64_t n_bins, d
     }
 }
 
+struct TallySet {
+    mxr_tally t[MXR_MAX_DETECTORS];
+};
+
+// The three arrays of a tally (blockIdx.y).  One launch for a run's histograms:
+// 16,384 bins with their allocation 11.9 us, by three fills 15.6.
+__global__ __launch_bounds__(256) void k_tally_clear(TallySet s) {
+    const mxr_tally &t = s.t[blockIdx.y];
+    for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; b < t.n_bins; b += (uint64_t)gridDim.x * blockDim.x) {
+        t.count[b] = 0;
+        t.sum_w[b] = 0.0;
+        t.sum_w2[b] = 0.0;
+    }
+}
+
 }  // namespace
+
+extern "C" mxr_status mxr_tally_clear(const mxr_tally *tallies, uint32_t n_tallies, void *hip_stream) {
+    if (n_tallies == 0) return MXR_OK;
+    if (!tallies) return mxr_host::set_error(MXR_E_INVALID, "null tallies");
+    if (n_tallies > MXR_MAX_DETECTORS) return mxr_host::set_error(MXR_E_INVALID, "more tallies than monitors an instrument can have");
+    TallySet s{};
+    uint64_t most = 0;
+    for (uint32_t i = 0; i < n_tallies; ++i) {
+        if (!tallies[i].count || !tallies[i].sum_w || !tallies[i].sum_w2)
+            return mxr_host::set_error(MXR_E_INVALID, "a tally has a null array");
+        s.t[i] = tallies[i];
+        most = std::max<uint64_t>(most, tallies[i].n_bins);
+    }
+    if (most == 0) return MXR_OK;
+    const unsigned blocks = (unsigned)std::min<uint64_t>((most + 255) / 256, 1ull << 14);
+    hipLaunchKernelGGL(k_tally_clear, dim3(blocks, n_tallies), dim3(256), 0, (hipStream_t)hip_stream, s);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        char buf[256];
+        snprintf(buf, sizeof buf, "tally clear launch: %s", hipGetErrorString(e));
+        return mxr_host::set_error(MXR_E_HIP, buf);
+    }
+    return MXR_OK;
+}
 
 extern "C" mxr_status mxr_batch_means(const double *sums, uint32_t R, uint64_t n_bins, uint64_t rays_per_replica,
                                       double *mean, double *rel, void *hip_stream) {
