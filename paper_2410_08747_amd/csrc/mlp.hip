@@ -396,14 +396,21 @@ struct StripLds {
     uint4 w2b[BACK ? 8 * 4 * 64 : 1], w3b[BACK ? 8 * 2 * 64 : 1];      // W2, W3
     uint2 w1[8 * 64];                                                  // W1^T
     float b1[kHid], b2[kHid], b3[64];
+    double red[BACK ? kSumBlocks : 1];                                 // the batch's weight sums, then their sum
     // transposed layers; before the first pass the parameters as they come
     uint16_t t[(kHid + 64) * kPassRows];
 };
 constexpr int kRawRow = kHid + 4;  // staged W2 rows, two banks apart
 static_assert((kHid * kRawRow + kHid * kOut) <= (kHid + 64) * kPassRows, "staging space");
 
+// Stages the weights, and (BACK) sums the batch's weight sums: one wave does it
+// beside the staging, in the order of a halving tree over the partials.
 template <bool K32, bool BACK>
-__device__ __forceinline__ void stage_weights(const uint16_t *w, StripLds<BACK> &S, int tid) {
+__device__ __forceinline__ void stage_weights(const uint16_t *w, const double *wsum, StripLds<BACK> &S, int tid) {
+    static_assert(kSumBlocks == 256 && kSumBlocks <= kStripThreads, "four partials a lane of one wave");
+    double part = 0.0;
+    if constexpr (BACK)
+        if (tid < (int)kSumBlocks) part = wsum[tid];
     uint16_t *raw = S.t, *raw3 = raw + kHid * kRawRow;
     uint4 c2[4], c3[2];
 #pragma unroll
@@ -436,7 +443,15 @@ __device__ __forceinline__ void stage_weights(const uint16_t *w, StripLds<BACK> 
         const int o = out_of(tid >> 4, (tid >> 2) & 3, tid & 3);
         S.b3[tid] = o >= 0 ? bf16_to_f32(w[kB3 + o]) : 0.f;
     }
+    if constexpr (BACK)
+        if (tid < (int)kSumBlocks) S.red[tid] = part;
     __syncthreads();
+    if constexpr (BACK)
+        if (tid < 64) {
+            double v = (S.red[tid] + S.red[tid + 128]) + (S.red[tid + 64] + S.red[tid + 192]);
+            for (int h = 32; h > 0; h >>= 1) v += __shfl_down(v, h, 64);
+            if (tid == 0) S.red[0] = v;
+        }
     for (int p = tid; p < 8 * 4 * 64; p += kStripThreads) {
         const int r = p & 15, q = (p >> 4) & 3, u = (p >> 6) & 3, t = p >> 8, m = row_of<K32>(t, r >> 2, r & 3);
         uint32_t e[8];
@@ -506,20 +521,9 @@ __global__ __launch_bounds__(kStripThreads) void k_strip(StripArgs f) {
     constexpr bool LAYERS = MODE == kForward || MODE == kGradient;
     __shared__ StripLds<BACK> S;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, q = lane >> 4;
+    stage_weights<K32>(f.w, f.wsum, S, tid);
     double wsum = 0.0;
-    if constexpr (BACK) {  // the batch's weight sum, the partials in one order in every work-group
-        static_assert(kSumBlocks <= kStripThreads, "a partial per thread");
-        double *red = (double *)S.t;
-        if (tid < (int)kSumBlocks) red[tid] = f.wsum[tid];
-        __syncthreads();
-        for (int h = kSumBlocks / 2; h > 0; h >>= 1) {
-            if (tid < h) red[tid] += red[tid + h];
-            __syncthreads();
-        }
-        wsum = red[0];
-        __syncthreads();
-    }
-    stage_weights<K32>(f.w, S, tid);
+    if constexpr (BACK) wsum = S.red[0];
     if constexpr (LAYERS) {  // the workspace's transposed weights, a share per work-group
         for (int i = blockIdx.x * kStripThreads + tid; i < kHid * kHid; i += gridDim.x * kStripThreads)
             f.wt[kW2 + (i % kHid) * kHid + i / kHid] = f.w[kW2 + i];
@@ -837,6 +841,12 @@ __global__ __launch_bounds__(kThreads) void k_reduce(const float *part, int grou
     __shared__ double rl[kGroupsMax];
     const int sub = threadIdx.x >> 4, c = (threadIdx.x & 15) * 4;
     const uint64_t p4 = (uint64_t)blockIdx.x * kReduceParams + c;
+    // a parameter a thread in the end; its Adam state arrives beside the partials
+    const uint64_t p = (uint64_t)blockIdx.x * kReduceParams + threadIdx.x;
+    const bool mine = threadIdx.x < kReduceParams && p < kParams;
+    float m0 = 0.f, v0 = 0.f, t0 = 0.f;
+    if constexpr (ADAM)
+        if (mine) m0 = A.m[p], v0 = A.v[p], t0 = A.theta[p];
     v4f acc = {0.f, 0.f, 0.f, 0.f};
     if (p4 < kParams) {
         v4f v[16];
@@ -859,18 +869,17 @@ __global__ __launch_bounds__(kThreads) void k_reduce(const float *part, int grou
         if (threadIdx.x == 0) *loss = rl[0];
     }
     __syncthreads();
-    const uint64_t p = (uint64_t)blockIdx.x * kReduceParams + threadIdx.x;
-    if (threadIdx.x >= kReduceParams || p >= kParams) return;
+    if (!mine) return;
     float gi = 0.f;
 #pragma unroll
     for (int u = 0; u < 16; ++u) gi += red[u][threadIdx.x];
     grad[p] = gi;
     if constexpr (ADAM) {
-        const float mi = A.b1 * A.m[p] + (1.f - A.b1) * gi;
-        const float vi = A.b2 * A.v[p] + (1.f - A.b2) * gi * gi;
+        const float mi = A.b1 * m0 + (1.f - A.b1) * gi;
+        const float vi = A.b2 * v0 + (1.f - A.b2) * gi * gi;
         A.m[p] = mi;
         A.v[p] = vi;
-        const float t = A.theta[p] - A.lr * (mi * A.c1) / (sqrtf(vi * A.c2) + A.eps);
+        const float t = t0 - A.lr * (mi * A.c1) / (sqrtf(vi * A.c2) + A.eps);
         A.theta[p] = t;
         A.wb[p] = f32_to_bf16(t);
     }
@@ -1195,10 +1204,14 @@ mxr_status mxr_mlp_train(const float *ctx, const double *y, const double *omega,
     if (ws_bytes < L.bytes) return fail(MXR_E_INVALID, "workspace of %llu bytes, %llu needed", (unsigned long long)ws_bytes, (unsigned long long)L.bytes);
     hipStream_t st = (hipStream_t)hip_stream;
     const uint64_t steps_per_epoch = (n_rows + B - 1) / B;
-    // partial weight sums: steps whose kSumBlocks doubles fit in the layer values' space
-    double *wsum = at<double>(ws, L, MXR_MLP_WS_Z1);
-    const uint64_t sum_steps = std::min<uint64_t>(
-        65535, (L.off[MXR_MLP_WS_PARTIAL] - L.off[MXR_MLP_WS_Z1]) / (kSumBlocks * sizeof(double)));
+    // partial weight sums of as many steps as fit: behind the partial gradients
+    // that batches of B rows write, or (if those fill their region) in the layer
+    // values' space, which training leaves unused
+    const uint64_t parts = strip_groups(B) * kParams * sizeof(float);
+    const uint64_t behind = kGroupsMax * kParams * sizeof(float) - parts;
+    const uint64_t layers = L.off[MXR_MLP_WS_PARTIAL] - L.off[MXR_MLP_WS_Z1];
+    double *wsum = behind > layers ? (double *)(at<char>(ws, L, MXR_MLP_WS_PARTIAL) + parts) : at<double>(ws, L, MXR_MLP_WS_Z1);
+    const uint64_t sum_steps = std::min<uint64_t>(65535, std::max(behind, layers) / (kSumBlocks * sizeof(double)));
     // per-epoch bijections i -> (a i + b) mod n_rows from a splitmix64 sequence
     uint64_t state = cfg->seed;
     auto next = [&state]() {
@@ -1230,8 +1243,6 @@ mxr_status mxr_mlp_train(const float *ctx, const double *y, const double *omega,
             if (!(cfg->lr > 0.f) || !(cfg->beta1 >= 0.f && cfg->beta1 < 1.f) ||
                 !(cfg->beta2 >= 0.f && cfg->beta2 < 1.f) || !(cfg->eps >= 0.f))
                 return fail(MXR_E_INVALID, "bad Adam hyper-parameters");
-            // the weight sums of as many steps as the layer values' space
-            // (unused here) holds, in one launch
             if (k % sum_steps == 0) {
                 const uint64_t steps = std::min<uint64_t>(sum_steps, steps_per_epoch - k);
                 hipLaunchKernelGGL(k_batch_wsum, dim3(kSumBlocks, (unsigned)steps), dim3(kThreads), 0, st, omega, n_rows,
