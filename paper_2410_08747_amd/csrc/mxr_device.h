@@ -2278,8 +2278,9 @@ __device__ __forceinline__ bool comp_powder(const DevComp &c, Stream &s, Ray &ra
     double e2x = dl[1] * e1z - dl[2] * e1y;
     double e2y = dl[2] * e1x - dl[0] * e1z;
     double e2z = dl[0] * e1y - dl[1] * e1x;
-    // the cone angle 2 asin(sarg) by its sine and cosine
-    const double st = 2.0 * sarg * sqrt(1.0 - sarg * sarg), ct = 1.0 - 2.0 * (sarg * sarg);
+    // the cone angle 2 asin(sarg) by its sine and cosine (1 - sarg is exact where
+    // 1 - sarg^2 would cancel, near backscattering)
+    const double st = 2.0 * sarg * sqrt((1.0 - sarg) * (1.0 + sarg)), ct = 1.0 - 2.0 * (sarg * sarg);
     double se, ce;
     sincos_turn(s.u((int)c.draw0 + 1), se, ce);
     double out[3] = {ct * dl[0] + st * (ce * e1x + se * e2x), ct * dl[1] + st * (ce * e1y + se * e2y),
