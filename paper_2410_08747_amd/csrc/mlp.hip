@@ -30,7 +30,7 @@ constexpr int kIn = MXR_MLP_IN, kHid = MXR_MLP_HIDDEN, kOut = MXR_MLP_OUT;
 constexpr uint64_t kW1 = 0, kB1 = kW1 + kIn * kHid, kW2 = kB1 + kHid, kB2 = kW2 + kHid * kHid;
 constexpr uint64_t kW3 = kB2 + kHid, kB3 = kW3 + kHid * kOut, kParams = kB3 + kOut;
 static_assert(kParams == MXR_MLP_PARAMS, "parameter layout");
-constexpr uint64_t kSplitRows = 1024;  // rows per partial gradient that the workspace has room for
+constexpr uint64_t kSplitRows = 1024;  // the workspace's room: a partial gradient per so many rows
 constexpr int kThreads = 256;
 
 typedef short v4s __attribute__((ext_vector_type(4)));
@@ -71,13 +71,6 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 __device__ __forceinline__ float fexp(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
 __device__ __forceinline__ float flog(float x) { return __builtin_amdgcn_logf(x) * 0.6931471805599453f; }
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
-
-__device__ __forceinline__ float silu(float z) { return z * frcp(1.0f + fexp(-z)); }
-
-__device__ __forceinline__ float silu_grad(float z) {
-    const float s = frcp(1.0f + fexp(-z));
-    return s * (1.0f + z * (1.0f - s));
-}
 
 // ------------------------------------------------------ small kernels --
 
@@ -987,11 +980,14 @@ Layout layout_for(uint64_t n) {
         n * kOut * 4, n * kOut * 2,     // dO, dO (bf16)
         n * kHid * 4, n * kHid * 2,     // dZ2, dZ2 (bf16)
         n * kHid * 4, n * kHid * 2,     // dZ1, dZ1 (bf16)
-        std::max<uint64_t>(splits_for(n), kGroupsMax) * kParams * 4,  // group partials of the gradient
+        // partial gradients: at most kGroupsMax are written (the size callers have
+        // been told is kept)
+        std::max<uint64_t>(splits_for(n), kGroupsMax) * kParams * 4,
         n * 3 * 8, n * 8, n * 8,        // gathered targets, weights, per-row loss
         (kSumBlocks + 2) * 8,           // partial sums of the weights
         kParams * 2,                    // W^T copies (bf16), same offsets as W
-        ((n + 15) / 16 * kHid * 2 + (n + 7) / 8 * kOut) * 4,  // unused
+        // the work-groups' losses, a double each (the size callers have been told is kept)
+        ((n + 15) / 16 * kHid * 2 + (n + 7) / 8 * kOut) * 4,
     };
     Layout L;
     uint64_t o = 0;
@@ -1151,7 +1147,6 @@ mxr_status mxr_mlp_loss_grad(const uint16_t *w, const float *ctx, const double *
     a.W = at<double>(ws, L, MXR_MLP_WS_W);
     a.row_loss = at<double>(ws, L, MXR_MLP_WS_ROWLOSS);
     a.part = at<float>(ws, L, MXR_MLP_WS_PARTIAL);
-    // the losses of the work-groups, in the unused tail of the regions
     a.loss_part = at<double>(ws, L, MXR_MLP_WS_COLS);
     const int groups = (int)strip_groups(n);
     hipLaunchKernelGGL(k_strip<kGradient>, dim3(groups), dim3(kStripThreads), 0, st, a);

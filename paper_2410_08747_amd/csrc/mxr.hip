@@ -115,7 +115,7 @@ __device__ __forceinline__ int mu_row_of(const DevComp &c, double E, uint32_t n_
 }
 
 // Apply component k of type T.  Returns false when the ray is absorbed.
-template <int T, bool LEDGER, bool TRACE, bool EXACT, int KW = kWalkRound>
+template <int T, bool LEDGER, bool TRACE, bool EXACT>
 __device__ __forceinline__ bool apply(const DevComp &c, int k, Ray &ray, Stream &s, uint64_t ray_id,
                                       const RunArgs &a, const double *mu_lds, uint32_t n_mat, uint32_t n_ebin,
                                       RayEnd &end, const LedgerLds &L) {
@@ -156,7 +156,7 @@ __device__ __forceinline__ bool apply(const DevComp &c, int k, Ray &ray, Stream 
             if constexpr (T == kPhantomStep)
                 tau = step_tau(g, q, dl, c.par[3], (int)c.aux[5], mu_lds + e * n_mat);
             else
-                tau = siddon_tau<EXACT, false, true, KW>(g, q, dl, mu_lds + e * n_mat);
+                tau = siddon_tau<EXACT, false, true>(g, q, dl, mu_lds + e * n_mat);
             ray.w = ray.w * exp(-tau);
         }
         if constexpr (T == MXR_MIRROR_ELLIPTIC) ok = comp_mirror(c, ray);
@@ -202,31 +202,31 @@ __device__ __forceinline__ bool apply(const DevComp &c, int k, Ray &ray, Stream 
     }
 }
 
-template <bool LEDGER, bool TRACE, bool EXACT, int KW = kWalkRound>
+template <bool LEDGER, bool TRACE, bool EXACT>
 __device__ __forceinline__ bool apply_dynamic(const DevComp &c, int k, Ray &ray, Stream &s, uint64_t ray_id,
                                               const RunArgs &a, const double *mu_lds, uint32_t n_mat,
                                               uint32_t n_ebin, RayEnd &end, const LedgerLds &L) {
 #define MXR_CASE(T) \
-    case T: return apply<T, LEDGER, TRACE, EXACT, KW>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+    case T: return apply<T, LEDGER, TRACE, EXACT>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
     switch (c.type) {
         MXR_CASE(MXR_SRC_RECT_CONE)
         case MXR_SRC_CONE_BEAM:
-            if (a.prop) return apply<kSrcConeProposal, LEDGER, TRACE, EXACT, KW>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
-            return apply<MXR_SRC_CONE_BEAM, LEDGER, TRACE, EXACT, KW>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+            if (a.prop) return apply<kSrcConeProposal, LEDGER, TRACE, EXACT>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+            return apply<MXR_SRC_CONE_BEAM, LEDGER, TRACE, EXACT>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
         MXR_CASE(MXR_SRC_GAUSSIAN)
         MXR_CASE(MXR_SLIT)
         MXR_CASE(MXR_BOX)
         case MXR_PHANTOM:
-            if (c.flags & 2u) return apply<kPhantomScatter, LEDGER, TRACE, EXACT, KW>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
-            if (c.flags & 1u) return apply<kPhantomStep, LEDGER, TRACE, EXACT, KW>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
-            return apply<MXR_PHANTOM, LEDGER, TRACE, EXACT, KW>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+            if (c.flags & 2u) return apply<kPhantomScatter, LEDGER, TRACE, EXACT>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+            if (c.flags & 1u) return apply<kPhantomStep, LEDGER, TRACE, EXACT>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+            return apply<MXR_PHANTOM, LEDGER, TRACE, EXACT>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
         MXR_CASE(MXR_MIRROR_ELLIPTIC)
         MXR_CASE(MXR_DCM)
         MXR_CASE(MXR_POWDER)
         MXR_CASE(MXR_LENS_CRL)
         case MXR_DETECTOR:
-            if (a.hits.count) return apply<kDetectorCollect, LEDGER, TRACE, EXACT, KW>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
-            return apply<MXR_DETECTOR, LEDGER, TRACE, EXACT, KW>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+            if (a.hits.count) return apply<kDetectorCollect, LEDGER, TRACE, EXACT>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+            return apply<MXR_DETECTOR, LEDGER, TRACE, EXACT>(c, k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
         default: break;
     }
 #undef MXR_CASE
@@ -274,8 +274,8 @@ template <>
 struct WavesHint<Chain<MXR_SRC_CONE_BEAM, kPhantomScatter, MXR_DETECTOR>> {
     static constexpr int value = 6;
 };
-// with the primary chords walked as a bundle 4 do (2e7 rays scattered once in
-// 256^3: 14.4 ms; 6 with 284 B of scratch 18.8, 8 with 350 B 23.7)
+// with the primary chords walked as a bundle 4 do (about 100 B of scratch; 2e7 rays
+// scattered once in 256^3: 14.4 ms; 6 with 284 B 18.8, 8 with 350 B 23.7)
 template <>
 struct WavesHint<Chain<MXR_SRC_CONE_BEAM, kPhantomScatterOnce, MXR_DETECTOR>> {
     static constexpr int value = 4;
@@ -312,13 +312,13 @@ struct BatchWavesHint<Chain<MXR_SRC_CONE_BEAM, MXR_PHANTOM, MXR_DETECTOR>> {
     static constexpr int value = 4;
 };
 
-template <bool LEDGER, bool TRACE, bool EXACT, int KW, int T, int... Rest>
+template <bool LEDGER, bool TRACE, bool EXACT, int T, int... Rest>
 __device__ __forceinline__ bool run_fixed(const DevInstr *ins, int k, Ray &ray, Stream &s, uint64_t ray_id,
                                           const RunArgs &a, const double *mu_lds, uint32_t n_mat,
                                           uint32_t n_ebin, RayEnd &end, const LedgerLds &L) {
-    if (!apply<T, LEDGER, TRACE, EXACT, KW>(ins->c[k], k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L)) return false;
+    if (!apply<T, LEDGER, TRACE, EXACT>(ins->c[k], k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L)) return false;
     if constexpr (sizeof...(Rest) > 0)
-        return run_fixed<LEDGER, TRACE, EXACT, KW, Rest...>(ins, k + 1, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+        return run_fixed<LEDGER, TRACE, EXACT, Rest...>(ins, k + 1, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
     return true;
 }
 
@@ -361,7 +361,7 @@ __device__ __forceinline__ TallyHit run_tallied(Chain<Ts...>, const DevInstr *in
     ray.w = 0.0;
     double factor = 0.0;
     if constexpr (T[0] == MXR_SRC_CONE_BEAM) factor = cone_direction(ins->c[0], s, ray, ray_id, a);
-    else live = apply<T[0], false, false, EXACT, KW>(ins->c[0], 0, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L) && live;
+    else live = apply<T[0], false, false, EXACT>(ins->c[0], 0, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L) && live;
     if constexpr (N == 4) {
         static_assert(T[1] == MXR_SLIT, "an aperture between the source and the phantom");
         live = comp_slit(ins->c[1], ray) && live;
@@ -419,18 +419,18 @@ constexpr bool ends_in_absorber(Chain<Ts...>) {
     else return false;
 }
 
-template <bool LEDGER, bool TRACE, bool EXACT, int KW = kWalkRound, int... Ts>
+template <bool LEDGER, bool TRACE, bool EXACT, int... Ts>
 __device__ __forceinline__ bool run_chain(Chain<Ts...>, const DevInstr *ins, Ray &ray, Stream &s, uint64_t ray_id,
                                           const RunArgs &a, const double *mu_lds, uint32_t n_mat,
                                           uint32_t n_ebin, RayEnd &end, const LedgerLds &L) {
     if constexpr (sizeof...(Ts) == 1 && ((Ts == kDynamic) && ...)) {
         const uint32_t n = ins->ncomp;
         for (uint32_t k = 0; k < n; ++k)
-            if (!apply_dynamic<LEDGER, TRACE, EXACT, KW>(ins->c[k], (int)k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L))
+            if (!apply_dynamic<LEDGER, TRACE, EXACT>(ins->c[k], (int)k, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L))
                 return false;
         return true;
     } else {
-        return run_fixed<LEDGER, TRACE, EXACT, KW, Ts...>(ins, 0, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
+        return run_fixed<LEDGER, TRACE, EXACT, Ts...>(ins, 0, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
     }
 }
 
@@ -510,8 +510,7 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_trace(const MXR_CONSTANT_PARA
         ray.E = 0.0;
         ray.w = 0.0;
         RayEnd end{kExited, -1, -1};
-        bool alive = run_chain<LEDGER, TRACE, EXACT, kWalkRound>(C{}, ins, ray, s, ray_id, a, mu_lds, n_mat,
-                                                                          n_ebin, end, L);
+        bool alive = run_chain<LEDGER, TRACE, EXACT>(C{}, ins, ray, s, ray_id, a, mu_lds, n_mat, n_ebin, end, L);
         if constexpr (LEDGER) {
             if (alive) atomicAdd(L.slots + 4 * ins->ncomp, ray.w);
         }

@@ -273,13 +273,6 @@ __device__ __forceinline__ bool plane_z0(double q[3], const double dl[3]) {
 // by VALU issue: 1e8 rays 4.45 -> 3.26 ms and 5.04 -> 4.20 ms.  (A polynomial
 // asin for the mirror and the crystals gave the beamline less than 1 %.)
 
-// A constant in scalar registers: a 64-bit one costs a polynomial's step two
-// moves into vector registers otherwise (the Gaussian source and crop 18 % of
-// their instructions).
-__device__ __forceinline__ double scalar(double c) {
-    return c;
-}
-
 // 1 / d, d positive or negative and normal with a normal reciprocal: two Newton
 // steps from the hardware's estimate (about 23 bits).
 __device__ __forceinline__ double rcp_normal(double d) {
@@ -319,8 +312,10 @@ __device__ __forceinline__ double rsqrt_normal(double x) {
     return h + h;
 }
 
-// log(u), 0 < u < 1 normal: u = 2^k m, m in [sqrt(1/2), sqrt 2), f = m - 1
-// (exact), s = f / (2 + f), log(1 + f) = 2 atanh(s) = f - f^2/2 + s (f^2/2 + R)
+// log(u), 0 < u < 1 normal, by the published reduction to [sqrt(1/2), sqrt 2) and
+// the atanh series (W. J. Cody and W. Waite, Software Manual for the Elementary
+// Functions, 1980, which also splits log 2; the last additions in the order of
+// fdlibm's log, Sun Microsystems, 1993): u = 2^k m, f = m - 1 (exact), s = f / (2 + f), log(1 + f) = 2 atanh(s) = f - f^2/2 + s (f^2/2 + R)
 // with the series R = 2 (s^2/3 + s^4/5 + ...) (|s| < 0.172: the first term left
 // out is below 2e-18), added smallest first to k log 2 in two parts (the first
 // of 32 bits, so that its multiples are exact).
@@ -332,17 +327,17 @@ __device__ __forceinline__ double log_unit(double u) {
     k = low ? k - 1 : k;
     const double f = m - 1.0, s = f * rcp_normal(2.0 + f), z = s * s, half = 0.5 * (f * f), kd = (double)k;
     double R = 2.0 / 21.0;
-    R = fma(z, R, scalar(2.0 / 19.0));
-    R = fma(z, R, scalar(2.0 / 17.0));
-    R = fma(z, R, scalar(2.0 / 15.0));
-    R = fma(z, R, scalar(2.0 / 13.0));
-    R = fma(z, R, scalar(2.0 / 11.0));
-    R = fma(z, R, scalar(2.0 / 9.0));
-    R = fma(z, R, scalar(2.0 / 7.0));
-    R = fma(z, R, scalar(2.0 / 5.0));
-    R = fma(z, R, scalar(2.0 / 3.0));
-    const double lo = fma(kd, scalar(kLog2Lo), s * fma(z, R, half));
-    return fma(kd, scalar(kLog2Hi), -((half - lo) - f));
+    R = fma(z, R, 2.0 / 19.0);
+    R = fma(z, R, 2.0 / 17.0);
+    R = fma(z, R, 2.0 / 15.0);
+    R = fma(z, R, 2.0 / 13.0);
+    R = fma(z, R, 2.0 / 11.0);
+    R = fma(z, R, 2.0 / 9.0);
+    R = fma(z, R, 2.0 / 7.0);
+    R = fma(z, R, 2.0 / 5.0);
+    R = fma(z, R, 2.0 / 3.0);
+    const double lo = fma(kd, kLog2Lo, s * fma(z, R, half));
+    return fma(kd, kLog2Hi, -((half - lo) - f));
 }
 
 // sin y and cos y for |y| <= pi/4 from their Maclaurin series through y^17
@@ -351,23 +346,23 @@ __device__ __forceinline__ double log_unit(double u) {
 __device__ __forceinline__ void sincos_quarter(double y, double &sn, double &cs) {
     const double y2 = y * y;
     double p = -1.0 / 355687428096000.0;
-    p = fma(y2, p, scalar(1.0 / 1307674368000.0));
-    p = fma(y2, p, scalar(-1.0 / 6227020800.0));
-    p = fma(y2, p, scalar(1.0 / 39916800.0));
-    p = fma(y2, p, scalar(-1.0 / 362880.0));
-    p = fma(y2, p, scalar(1.0 / 5040.0));
-    p = fma(y2, p, scalar(-1.0 / 120.0));
-    p = fma(y2, p, scalar(1.0 / 6.0));
+    p = fma(y2, p, 1.0 / 1307674368000.0);
+    p = fma(y2, p, -1.0 / 6227020800.0);
+    p = fma(y2, p, 1.0 / 39916800.0);
+    p = fma(y2, p, -1.0 / 362880.0);
+    p = fma(y2, p, 1.0 / 5040.0);
+    p = fma(y2, p, -1.0 / 120.0);
+    p = fma(y2, p, 1.0 / 6.0);
     sn = fma(-(y * y2), p, y);
     double q = 1.0 / 6402373705728000.0;
-    q = fma(y2, q, scalar(-1.0 / 20922789888000.0));
-    q = fma(y2, q, scalar(1.0 / 87178291200.0));
-    q = fma(y2, q, scalar(-1.0 / 479001600.0));
-    q = fma(y2, q, scalar(1.0 / 3628800.0));
-    q = fma(y2, q, scalar(-1.0 / 40320.0));
-    q = fma(y2, q, scalar(1.0 / 720.0));
-    q = fma(y2, q, scalar(-1.0 / 24.0));
-    q = fma(y2, q, scalar(0.5));
+    q = fma(y2, q, -1.0 / 20922789888000.0);
+    q = fma(y2, q, 1.0 / 87178291200.0);
+    q = fma(y2, q, -1.0 / 479001600.0);
+    q = fma(y2, q, 1.0 / 3628800.0);
+    q = fma(y2, q, -1.0 / 40320.0);
+    q = fma(y2, q, 1.0 / 720.0);
+    q = fma(y2, q, -1.0 / 24.0);
+    q = fma(y2, q, 0.5);
     cs = fma(-y2, q, 1.0);
 }
 
@@ -1309,11 +1304,12 @@ __device__ __forceinline__ double step_tau(const PhantomGeo &g, const double q[3
 // phantom with 36 occupied layers, 2e5 rays: 26.1 us with the looks, 21.9
 // without; 3e6 rays 116 either way; a 128^3 one, 1e6 rays: 62 and 95 us).
 //
-// What bounds it now: the source, the tally's atomics and the latency of the
-// loads, no longer the walk.  1e9 rays through 256^3 voxels at 0 / 0.785 rad,
-// event walk of every ray that reaches the monitor 33.3 / 48 ms, this
-// 29.4 / 31.3 ms; 2e7 rays in wide strata (256^2) through 512^3: 3.2 -> 0.76
-// ms and 3.7 -> 1.0 ms.
+// What bounds its kernel: VALU issue, 0.8 of the rate in the tiled image kernel,
+// the source and the ray's share of the looks before the stretches.  A ray id a
+// lane and without tiles, 1e9 rays through 256^3 voxels at 0 / 0.785 rad, event walk
+// of every ray that reaches the monitor 33.3 / 48 ms, this 29.4 / 31.3 ms (in tiles
+// 16.5 ms); 2e7 rays in wide strata (256^2) through 512^3: 3.2 -> 0.76 ms and 3.7 ->
+// 1.0 ms.
 constexpr float kBundleSlack = 0.0078125f, kBundleNarrow = 6.0f;
 constexpr int kBundleDim = 2048, kBundleWide = 4, kBrickWide = 3;
 constexpr int kBundleLayers = 64;
