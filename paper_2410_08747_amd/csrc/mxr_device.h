@@ -1382,19 +1382,23 @@ __device__ __forceinline__ double add_run(double mu, double len, double tau) {
 template <class Run>
 __device__ __forceinline__ void turn_run(Run &run, double t, double a_out, uint32_t m, const double *__restrict__ mu_row) {
     const double tc = max_f64(min_f64(t, a_out), run.a_start);
-    const double tau = add_run(run.mu, tc - run.a_start, run.tau);
     if constexpr (sizeof(Run) > sizeof(OpenRun)) {
-        if (run.mu > 0.0 && tc > run.a_start) {  // as close_run
-            if (!run.hit.found && tau >= run.tau_star) {
-                run.hit.found = true;
-                run.hit.s = run.a_start + (run.tau_star - run.tau) / run.mu;
-                run.hit.m = run.m;
+        if (tc > run.a_start) {  // as close_run
+            const double tau = fma(run.mu, tc - run.a_start, run.tau);
+            if (run.mu > 0.0) {
+                if (!run.hit.found && tau >= run.tau_star) {
+                    run.hit.found = true;
+                    run.hit.s = run.a_start + (run.tau_star - run.tau) / run.mu;
+                    run.hit.m = run.m;
+                }
+                run.hit.last_end = tc;
+                run.hit.last_m = run.m;
             }
-            run.hit.last_end = tc;
-            run.hit.last_m = run.m;
+            run.tau = tau;
         }
+    } else {
+        run.tau = add_run(run.mu, tc - run.a_start, run.tau);
     }
-    run.tau = tau;
     run.a_start = tc;
     run.m = m;
     run.mu = mu_row[m];
