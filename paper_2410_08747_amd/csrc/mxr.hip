@@ -964,6 +964,7 @@ __global__ __launch_bounds__(kBlock) void k_mu_energy_major(const double *T, uin
 // materials (out[1..3] start at ~0 and out[0], out[4..6], out[8] at 0).  WORDS: rows of x start at multiples of four bytes,
 // so a brick's row is one 32-bit load (a 512^3 volume in one pass of
 // neighbouring loads; a lane per row of single bytes took 584 us there).
+constexpr int kScanWords = 9;
 template <bool WORDS>
 __global__ __launch_bounds__(kBlock) void k_phantom_scan(const uint8_t *vol, uint32_t nx, uint32_t ny, uint32_t nz,
                                                         uint8_t *bricks, unsigned int *out) {
@@ -976,33 +977,39 @@ __global__ __launch_bounds__(kBlock) void k_phantom_scan(const uint8_t *vol, uin
     unsigned int mx = 0, mixed = 0, lo[3] = {~0u, ~0u, ~0u}, hi[3] = {0u, 0u, 0u};
     for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         const uint32_t x0 = (i % bx) * 4, y0 = (i / bx) % by * 4, z0 = i / bx / by * 4;
-        const uint32_t x1 = x0 + 4 < nx ? x0 + 4 : nx, y1 = y0 + 4 < ny ? y0 + 4 : ny, z1 = z0 + 4 < nz ? z0 + 4 : nz;
+        const uint32_t x1 = x0 + 4 < nx ? x0 + 4 : nx;
         const uint32_t m0 = vol[((uint64_t)z0 * ny + y0) * nx + x0];
-        uint32_t differ = 0;
-        for (uint32_t z = z0; z < z1; ++z)
-            for (uint32_t y = y0; y < y1; ++y) {
-                const uint8_t *row = vol + ((uint64_t)z * ny + y) * nx + x0;
-                uint32_t w = m0 * 0x01010101u;
-                if constexpr (WORDS) {
-                    w = *(const uint32_t *)row;
-                } else {
-                    for (uint32_t x = 0; x < x1 - x0; ++x) w = (w & ~(0xFFu << (8 * x))) | ((uint32_t)row[x] << (8 * x));
-                }
-                const uint32_t d = w ^ (m0 * 0x01010101u);
-                differ |= d;
-                for (uint32_t x = 0; x < 4; ++x) mx = ((w >> (8 * x)) & 0xFFu) > mx ? (w >> (8 * x)) & 0xFFu : mx;
-                // first and last byte of the row that is not background
-                const uint32_t e = (w ^ (bg * 0x01010101u)) & (~0u >> (8 * (4 - (x1 - x0))));
-                if (e != 0) {
-                    const uint32_t first = x0 + (uint32_t)__builtin_ctz(e) / 8, last = x0 + (31 - (uint32_t)__builtin_clz(e)) / 8 + 1;
-                    lo[0] = first < lo[0] ? first : lo[0];
-                    hi[0] = last > hi[0] ? last : hi[0];
-                    lo[1] = y < lo[1] ? y : lo[1];
-                    hi[1] = y + 1 > hi[1] ? y + 1 : hi[1];
-                    lo[2] = z < lo[2] ? z : lo[2];
-                    hi[2] = z + 1 > hi[2] ? z + 1 : hi[2];
-                }
+        uint32_t differ = 0, words[16];
+        // (rows past the volume repeat its last ones)
+#pragma unroll
+        for (uint32_t r = 0; r < 16; ++r) {
+            const uint32_t y = y0 + r % 4 < ny ? y0 + r % 4 : ny - 1, z = z0 + r / 4 < nz ? z0 + r / 4 : nz - 1;
+            const uint8_t *row = vol + ((uint64_t)z * ny + y) * nx + x0;
+            if constexpr (WORDS) {
+                words[r] = *(const uint32_t *)row;
+            } else {
+                words[r] = m0 * 0x01010101u;
+                for (uint32_t x = 0; x < x1 - x0; ++x) words[r] = (words[r] & ~(0xFFu << (8 * x))) | ((uint32_t)row[x] << (8 * x));
             }
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < 16; ++r) {
+            const uint32_t y = y0 + r % 4 < ny ? y0 + r % 4 : ny - 1, z = z0 + r / 4 < nz ? z0 + r / 4 : nz - 1, w = words[r];
+            const uint32_t d = w ^ (m0 * 0x01010101u);
+            differ |= d;
+            for (uint32_t x = 0; x < 4; ++x) mx = ((w >> (8 * x)) & 0xFFu) > mx ? (w >> (8 * x)) & 0xFFu : mx;
+            // first and last byte of the row that is not background
+            const uint32_t e = (w ^ (bg * 0x01010101u)) & (~0u >> (8 * (4 - (x1 - x0))));
+            if (e != 0) {
+                const uint32_t first = x0 + (uint32_t)__builtin_ctz(e) / 8, last = x0 + (31 - (uint32_t)__builtin_clz(e)) / 8 + 1;
+                lo[0] = first < lo[0] ? first : lo[0];
+                hi[0] = last > hi[0] ? last : hi[0];
+                lo[1] = y < lo[1] ? y : lo[1];
+                hi[1] = y + 1 > hi[1] ? y + 1 : hi[1];
+                lo[2] = z < lo[2] ? z : lo[2];
+                hi[2] = z + 1 > hi[2] ? z + 1 : hi[2];
+            }
+        }
         bricks[i] = differ ? (uint8_t)255 : (uint8_t)m0;
         mixed += differ != 0;
     }
@@ -1015,11 +1022,14 @@ __global__ __launch_bounds__(kBlock) void k_phantom_scan(const uint8_t *vol, uin
         }
     __syncthreads();
     if (threadIdx.x == 0) {
-        atomicMax(out, red[0]);
-        atomicAdd(out + 8, red[7]);
+        // only what still improves on the results goes there (1024 groups' atomics on
+        // one line had taken most of the 256^3 scan)
+        auto now = [&](int k) { return __hip_atomic_load(out + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        if (red[0] > now(0)) atomicMax(out, red[0]);
+        if (red[7] > 0) atomicAdd(out + 8, red[7]);
         for (int d = 0; d < 3; ++d) {
-            atomicMin(out + 1 + d, red[1 + d]);
-            atomicMax(out + 4 + d, red[4 + d]);
+            if (red[1 + d] < now(1 + d)) atomicMin(out + 1 + d, red[1 + d]);
+            if (red[4 + d] > now(4 + d)) atomicMax(out + 4 + d, red[4 + d]);
         }
         if (blockIdx.x == 0) out[7] = bg;
     }
@@ -1571,17 +1581,22 @@ mxr_status mxr_instrument_create(const mxr_instrument_desc *desc, mxr_instrument
         ins->n_cu < 1)
         ins->n_cu = 256;
     ins->mu_dev = nullptr;
+    unsigned *scan = nullptr;
     if (d.phantom >= 0) {
-        // the staged attenuation table, and the brick map behind it
+        // the staged attenuation table, the brick map behind it, and the words of the
+        // scan below (an allocation and a release of their own cost 35 us of a
+        // 640 us creation)
         const uint32_t n_mu = d.n_mat * d.n_ebin;
         const uint32_t *dims = d.c[d.phantom].dims;
         const size_t n_bricks = (size_t)((dims[0] + 3) / 4) * ((dims[1] + 3) / 4) * ((dims[2] + 3) / 4);
-        e = hipMalloc((void **)&ins->mu_dev, (size_t)n_mu * sizeof(double) + n_bricks);
+        const size_t scan_at = ((size_t)n_mu * sizeof(double) + n_bricks + 15) / 16 * 16;
+        e = hipMalloc((void **)&ins->mu_dev, scan_at + kScanWords * sizeof(unsigned));
         if (e != hipSuccess) {
             delete ins;
             return fail(MXR_E_NOMEM, "hipMalloc of the attenuation table: %s", hipGetErrorString(e));
         }
         d.bricks = (const uint8_t *)(ins->mu_dev + n_mu);
+        scan = (unsigned *)((char *)ins->mu_dev + scan_at);
         hipLaunchKernelGGL(k_mu_energy_major, dim3((n_mu + kBlock - 1) / kBlock), dim3(kBlock), 0, 0,
                            (const double *)d.c[d.phantom].data1, d.n_mat, d.n_ebin, ins->mu_dev);
         e = hipGetLastError();
@@ -1596,19 +1611,17 @@ mxr_status mxr_instrument_create(const mxr_instrument_desc *desc, mxr_instrument
         // one pass over the volume: every material id must index the mu
         // table, and the box of voxels unlike the corner bounds the walk
         DevComp &c = d.c[d.phantom];
-        unsigned int *dscan = nullptr, hs[9] = {0u, ~0u, ~0u, ~0u, 0u, 0u, 0u, 0u, 0u};
-        e = hipMalloc((void **)&dscan, sizeof hs);
-        if (e == hipSuccess) e = hipMemcpy(dscan, hs, sizeof hs, hipMemcpyHostToDevice);
+        unsigned hs[kScanWords] = {0u, ~0u, ~0u, ~0u, 0u, 0u, 0u, 0u, 0u};
+        e = hipMemcpy(scan, hs, sizeof hs, hipMemcpyHostToDevice);
         if (e == hipSuccess) {
             const uint64_t nb = (uint64_t)((c.dims[0] + 3) / 4) * ((c.dims[1] + 3) / 4) * ((c.dims[2] + 3) / 4);
             const unsigned groups = (unsigned)std::min<uint64_t>((nb + kBlock - 1) / kBlock, 2048);
             const bool words = c.dims[0] % 4 == 0 && ((uintptr_t)c.data0 & 3) == 0;
             hipLaunchKernelGGL(words ? k_phantom_scan<true> : k_phantom_scan<false>, dim3(groups), dim3(kBlock), 0, 0,
-                               (const uint8_t *)c.data0, c.dims[0], c.dims[1], c.dims[2], (uint8_t *)d.bricks, dscan);
+                               (const uint8_t *)c.data0, c.dims[0], c.dims[1], c.dims[2], (uint8_t *)d.bricks, scan);
             e = hipGetLastError();
         }
-        if (e == hipSuccess) e = hipMemcpy(hs, dscan, sizeof hs, hipMemcpyDeviceToHost);
-        if (dscan) (void)hipFree(dscan);
+        if (e == hipSuccess) e = hipMemcpy(hs, scan, sizeof hs, hipMemcpyDeviceToHost);
         if (e != hipSuccess) {
             (void)hipFree(ins->mu_dev);
             delete ins;
